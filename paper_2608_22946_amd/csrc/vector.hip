@@ -37,8 +37,6 @@ __device__ __forceinline__ D2 cdot(T a, T b) {   // conj(a) * b
     return {ar * br + ai * bi, ar * bi - ai * br};
 }
 
-__device__ __forceinline__ double wave_sum(double v) { return wave_sum_f64(v); }
-
 // Krylov basis vectors (V_j in the projections and updates, Z_j in the combination) are
 // loaded with the non-temporal hint: at 2h the K_2h basis alone is up to 0.5 GB, and
 // streaming it through the last-level cache evicted the velocity, D^-1 and V-cycle vectors
@@ -71,32 +69,92 @@ __device__ __forceinline__ c64 ldnt(const c64 *p) {
 // blocks (one element per step: unrolled steps measured slower).
 __device__ __forceinline__ long long elem_index() { return blockIdx.x * (long long)blockDim.x + threadIdx.x; }
 
-// Block-reduce NS complex sums, store them as this block's partials, then
-// return true in the last block to arrive (which may read every block's partials).
 constexpr int kRedThreads = 1024;      // threads per reduction block (16 wavefronts)
 constexpr int kRedWaves = kRedThreads / 64;
 
+__device__ __forceinline__ double f64_of(unsigned lo, unsigned hi) {
+    return __longlong_as_double(((long long)hi << 32) | lo);
+}
+// a and b exchanged between the halves of the wavefront (lanes 32..63 of a against lanes 0..31 of b;
+// ROWS: the odd 16-lane rows of a against the even rows of b), then added: the sum holds the two
+// halves' (rows') sums of a in the even half (rows) and those of b in the odd one
+template <bool ROWS>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    const long long p = __double_as_longlong(a), q = __double_as_longlong(b);
+    if constexpr (ROWS) {
+        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)p, (unsigned)q, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(p >> 32), (unsigned)(q >> 32), false, false);
+        return f64_of(lo[0], hi[0]) + f64_of(lo[1], hi[1]);
+    } else {
+        const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)p, (unsigned)q, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(p >> 32), (unsigned)(q >> 32), false, false);
+        return f64_of(lo[0], hi[0]) + f64_of(lo[1], hi[1]);
+    }
+}
+
+// Sums of N doubles over the wavefront, written to out[0..N).  Two exchange steps halve the
+// number of registers while they halve the lanes that carry each value, so that the 16-lane sums
+// run on N / 4 registers: 165 vector instructions for the 30 sums of a five-vector Gram matrix
+// against 750 for thirty separate wavefront sums, which were most of a small reduction's time
+// (the Gram kernel on 729 nodes took 15.7 us).
+template <int N>
+__device__ __forceinline__ void wave_sums(const double (&v)[N], double *out) {
+    constexpr int H = (N + 1) / 2, Q = (H + 1) / 2;
+    double h[H], q[Q];
+#pragma unroll
+    for (int i = 0; i < H; ++i) h[i] = swap_add<false>(v[2 * i], 2 * i + 1 < N ? v[2 * i + 1] : 0.0);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        // rows 0, 1, 2, 3 of q[i]: values 4i, 4i + 2, 4i + 1, 4i + 3
+        q[i] = swap_add<true>(h[2 * i], 2 * i + 1 < H ? h[2 * i + 1] : 0.0);
+        q[i] += dpp_double<0xB1>(q[i]);    // quad_perm [1,0,3,2]
+        q[i] += dpp_double<0x4E>(q[i]);    // quad_perm [2,3,0,1]
+        q[i] += dpp_double<0x124>(q[i]);   // row_ror:4
+        q[i] += dpp_double<0x128>(q[i]);   // row_ror:8
+    }
+    const int lane = threadIdx.x & 63, row = lane >> 4;
+    if ((lane & 15) == 0) {
+        const int k = ((row & 1) << 1) | (row >> 1);
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            if (4 * i + k < N) out[4 * i + k] = q[i];
+    }
+}
+
+// Block sums of NS complex values.  With one block in the launch the totals are in `out` at once;
+// otherwise they are stored as this block's partials and sum_partials adds them up.  Returns true
+// in the last block to arrive.
 template <int NS>
-__device__ bool reduce_partials(D2 (&acc)[NS], const RedBuf &rb) {
+__device__ bool reduce_partials(const D2 (&acc)[NS], const RedBuf &rb, D2 *out) {
     __shared__ double red[kRedWaves][2 * kSlots];
     __shared__ bool last;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int w = threadIdx.x >> 6;
+    {
+        double v[2 * NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        double r = wave_sum(acc[s].r), i = wave_sum(acc[s].i);
-        if (lane == 0) {
-            red[w][2 * s] = r;
-            red[w][2 * s + 1] = i;
+        for (int s = 0; s < NS; ++s) {
+            v[2 * s] = acc[s].r;
+            v[2 * s + 1] = acc[s].i;
         }
+        wave_sums(v, red[w]);
     }
     __syncthreads();
     if (threadIdx.x < 2 * NS) {
         double v = 0.0;
+#pragma unroll
         for (int k = 0; k < kRedWaves; ++k) v += red[k][threadIdx.x];
-        partial_store(rb.partials + (size_t)blockIdx.x * 2 * kSlots + threadIdx.x, v);
-        stores_done();
+        if (gridDim.x == 1) {
+            if (threadIdx.x & 1)
+                out[threadIdx.x >> 1].i = v;
+            else
+                out[threadIdx.x >> 1].r = v;
+        } else {
+            partial_store(rb.partials + (size_t)blockIdx.x * 2 * kSlots + threadIdx.x, v);
+            stores_done();
+        }
     }
     __syncthreads();
+    if (gridDim.x == 1) return true;
     if (threadIdx.x == 0) last = take_ticket(rb.counter, gridDim.x);
     __syncthreads();
     return last;
@@ -108,6 +166,7 @@ __device__ bool reduce_partials(D2 (&acc)[NS], const RedBuf &rb) {
 // the G group sums are added in order.
 template <int NS>
 __device__ void sum_partials(const RedBuf &rb, D2 *out) {
+    if (gridDim.x == 1) return;   // reduce_partials has written the totals
     constexpr int NQ = 2 * NS;
     constexpr int G = kRedThreads / NQ > 0 ? kRedThreads / NQ : 1;
     __shared__ double grp[kRedThreads];
@@ -143,14 +202,30 @@ __device__ void state_init(KState *st, double beta) {
     st->g[0][0] = beta;
 }
 
-// Column k of the Hessenberg matrix: cr (k+1 entries, rotated in place) and
+// The rotations of a state, copied to LDS by the last block's threads while the sums are still
+// under way: the one thread that builds a column reads them one after the other, and from memory
+// each would cost it a round trip (the ten-vector projection on 35k nodes took 20 us).
+struct Rotations {
+    double cs[kMMax], sn[kMMax][2], g[2], vs0, wn;
+};
+__device__ __forceinline__ void load_rotations(Rotations &r, const KState *st, int k) {
+    const int t = threadIdx.x;
+    if (t < k) r.cs[t] = st->cs[t];
+    if (t >= 64 && t < 64 + 2 * k) r.sn[(t - 64) >> 1][t & 1] = st->sn[(t - 64) >> 1][t & 1];
+    if (t >= 128 && t < 130) r.g[t & 1] = st->g[k][t & 1];
+    if (t == 130) r.vs0 = st->vs0;
+    if (t == 131) r.wn = st->wn;
+}
+
+// Column K of the Hessenberg matrix: cr (K+1 entries, rotated in place) and
 // h_{k+1,k}; apply the previous rotations, build the one annihilating h_{k+1,k},
-// rotate g.  One thread runs it; cr lives in LDS so that the loops with a
-// run-time bound need no private (scratch) array and add nothing to the
-// register budget of the streaming loop that precedes the epilogue.
-__device__ void givens_column(KState *st, int k, double (*cr)[2], double hk1) {
+// rotate g.  One thread runs it; cr and the rotations live in LDS, so that nothing adds to the
+// register budget of the streaming loop that precedes the epilogue.  wn: ||w||.
+template <int k>
+__device__ void givens_column(KState *st, const Rotations &rot, double (*cr)[2], double hk1, double wn) {
+#pragma unroll
     for (int j = 0; j < k; ++j) {
-        const double c = st->cs[j], sr = st->sn[j][0], si = st->sn[j][1];
+        const double c = rot.cs[j], sr = rot.sn[j][0], si = rot.sn[j][1];
         const double ar = cr[j][0], ai = cr[j][1], br = cr[j + 1][0], bi = cr[j + 1][1];
         // [c s; -conj(s) c] [a; b]
         cr[j][0] = c * ar + (sr * br - si * bi);
@@ -180,8 +255,9 @@ __device__ void givens_column(KState *st, int k, double (*cr)[2], double hk1) {
         st->H[j][k][0] = cr[j][0];
         st->H[j][k][1] = cr[j][1];
     }
-    const double gr = st->g[k][0], gi = st->g[k][1];
-    st->g[k + 1][0] = -(sr * gr + si * gi);
+    const double gr = rot.g[0], gi = rot.g[1];
+    const double gnr = -(sr * gr + si * gi);
+    st->g[k + 1][0] = gnr;
     st->g[k + 1][1] = -(sr * gi - si * gr);
     st->g[k][0] = c * gr;
     st->g[k][1] = c * gi;
@@ -189,10 +265,10 @@ __device__ void givens_column(KState *st, int k, double (*cr)[2], double hk1) {
     st->hk1 = hk1;
     // h_{k+1,k} and ||w|| carry the same scale (also in column 0, built from the
     // unnormalised first vector), so the test is scale-free
-    const bool ok = hk1 > kBreakdown * st->wn;
+    const bool ok = hk1 > kBreakdown * wn;
     st->scale = ok ? 1.0 / hk1 : 0.0;
     if (!ok) st->breakdown = 1;
-    if (!(hk1 == hk1) || !(st->g[k + 1][0] == st->g[k + 1][0])) st->nonfinite = 1;
+    if (!(hk1 == hk1) || !(gnr == gnr)) st->nonfinite = 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -225,8 +301,13 @@ __global__ void __launch_bounds__(1024) k_dots(Ptrs<T, NV> P, const T *__restric
         for (int j = 0; j < NV; ++j) acc[j] = acc[j] + cdot(ldnt(P.v[j] + i), wi);
         if (NORM) acc[NV] = acc[NV] + D2{(double)wi.re * wi.re + (double)wi.im * wi.im, 0.0};
     }
-    if (!reduce_partials<NS>(acc, rb)) return;
     __shared__ D2 tot[kSlots];
+    if (!reduce_partials<NS>(acc, rb, tot)) return;
+    __shared__ Rotations rot;
+    if constexpr (EPI == EPI_ARNOLDI_SEL && NV > 0) {
+        load_rotations(rot, st, NV - 1);
+        if (gridDim.x == 1) __syncthreads();   // else sum_partials orders it
+    }
     sum_partials<NS>(rb, tot);
     if (threadIdx.x == 0) {
         if (EPI == EPI_STORE) {
@@ -242,12 +323,12 @@ __global__ void __launch_bounds__(1024) k_dots(Ptrs<T, NV> P, const T *__restric
             }
             st->reorth = 1;
             st->wn = 0.0;   // no norm in this pass: only an exactly vanishing w - V h counts as breakdown
-        } else if (EPI == EPI_ARNOLDI_SEL && NV > 0) {
+        } else if constexpr (EPI == EPI_ARNOLDI_SEL && NV > 0) {
             // selective second pass: if the first projection keeps at least
             // kReorthEta of ||w||^2, w - V h1 is orthogonal to a few units of
             // roundoff and the second pass is skipped.
             __shared__ double col[kMMax + 1][2];
-            tot[0] = {tot[0].r * st->vs0, tot[0].i * st->vs0};   // onto the normalised V_0
+            tot[0] = {tot[0].r * rot.vs0, tot[0].i * rot.vs0};   // onto the normalised V_0
             double c2 = 0.0;
             for (int j = 0; j < NV; ++j) {
                 st->h1[j][0] = col[j][0] = tot[j].r;
@@ -255,14 +336,15 @@ __global__ void __launch_bounds__(1024) k_dots(Ptrs<T, NV> P, const T *__restric
                 c2 += tot[j].r * tot[j].r + tot[j].i * tot[j].i;
             }
             const double w2 = tot[NS - 1].r, r2 = w2 - c2;
-            st->wn = sqrt(w2);
+            const double wn = sqrt(w2);
+            st->wn = wn;
             if (r2 >= kReorthEta * w2) {
                 for (int j = 0; j < NV; ++j) {
                     st->h2[j][0] = tot[j].r;
                     st->h2[j][1] = tot[j].i;
                 }
                 st->reorth = 0;
-                givens_column(st, NV - 1, col, sqrt(r2));
+                givens_column<NV - 1>(st, rot, col, sqrt(r2), wn);
             } else {
                 st->reorth = 1;
             }
@@ -317,12 +399,15 @@ __global__ void __launch_bounds__(1024) k_axpy_dots(Ptrs<T, NV> P, T *__restrict
         for (int j = 0; j < NV; ++j) acc[j] = acc[j] + cdot(v[j], wi);
         acc[NV] = acc[NV] + D2{(double)wi.re * wi.re + (double)wi.im * wi.im, 0.0};
     }
-    if (!reduce_partials<NV + 1>(acc, rb)) return;
     __shared__ D2 tot[kSlots];
+    if (!reduce_partials<NV + 1>(acc, rb, tot)) return;
+    __shared__ Rotations rot;
+    load_rotations(rot, st, NV - 1);
+    if (gridDim.x == 1) __syncthreads();   // else sum_partials orders it
     sum_partials<NV + 1>(rb, tot);
     if (threadIdx.x == 0) {
         __shared__ double col[kMMax + 1][2];
-        tot[0] = {tot[0].r * st->vs0, tot[0].i * st->vs0};   // onto the normalised V_0
+        tot[0] = {tot[0].r * rot.vs0, tot[0].i * rot.vs0};   // onto the normalised V_0
         double c2 = 0.0;
         for (int j = 0; j < NV; ++j) {
             st->h2[j][0] = tot[j].r;
@@ -333,7 +418,7 @@ __global__ void __launch_bounds__(1024) k_axpy_dots(Ptrs<T, NV> P, T *__restrict
         }
         // ||w - V h2||^2 = ||w||^2 - ||h2||^2 for orthonormal V
         const double hk1 = sqrt(fmax(tot[NV].r - c2, 0.0));
-        givens_column(st, NV - 1, col, hk1);
+        givens_column<NV - 1>(st, rot, col, hk1, rot.wn);
         reset_ticket(rb.counter);
     }
 }
@@ -467,6 +552,81 @@ __global__ void __launch_bounds__(256) k_convert_scaled(const TI *__restrict__ x
     y[i] = to_stored<TO, RA>((RA)v.re * mi, (RA)v.im * mi, mo);
 }
 
+// Least-squares coefficients from the Gram sums of a short basis (NP <= 5), by one thread with
+// every array in registers: the loops are unrolled and a vanishing pivot clears the rest of the
+// factor instead of ending the loops.  Same operations in the same order as the general solve
+// below, whose LDS round trips dominated the epilogue.
+template <int NP>
+__device__ __forceinline__ void gram_solve(const D2 *tot, KState *st) {
+    constexpr int m = NP - 1;
+    auto idx = [](int a, int b) { return a * NP - a * (a - 1) / 2 + (b - a); };   // (a, b), a <= b
+    double g[m][m][2], gr0[m][2];   // <P_{i+1}, P_{j+1}> for i >= j, and <P_{i+1}, P_0>
+#pragma unroll
+    for (int i = 0; i < m; ++i) {
+        const D2 t0 = tot[idx(0, i + 1)];
+        gr0[i][0] = t0.r;
+        gr0[i][1] = -t0.i;
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            const D2 t = tot[idx(j + 1, i + 1)];
+            g[i][j][0] = t.r;
+            g[i][j][1] = -t.i;
+        }
+    }
+    double Lr[m][m], Li[m][m], ur[m], ui[m], yr[m], yi[m];
+    bool live[m];
+#pragma unroll
+    for (int j = 0; j < m; ++j) {
+        double d = g[j][j][0];
+#pragma unroll
+        for (int k = 0; k < j; ++k) d -= Lr[j][k] * Lr[j][k] + Li[j][k] * Li[j][k];
+        live[j] = (j == 0 || live[j > 0 ? j - 1 : 0]) && d > 1e-24 * g[j][j][0];
+        const double ljj = live[j] ? sqrt(d) : 1.0;
+        Lr[j][j] = ljj;
+        Li[j][j] = 0.0;
+#pragma unroll
+        for (int i = j + 1; i < m; ++i) {
+            double ar = g[i][j][0], ai = g[i][j][1];
+#pragma unroll
+            for (int k = 0; k < j; ++k) {   // - L_ik conj(L_jk)
+                ar -= Lr[i][k] * Lr[j][k] + Li[i][k] * Li[j][k];
+                ai -= Li[i][k] * Lr[j][k] - Lr[i][k] * Li[j][k];
+            }
+            Lr[i][j] = live[j] ? ar / ljj : 0.0;
+            Li[i][j] = live[j] ? ai / ljj : 0.0;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < m; ++i) {   // L u = rhs, rhs_i = <P_{i+1}, P_0>
+        double ar = gr0[i][0], ai = gr0[i][1];
+#pragma unroll
+        for (int k = 0; k < i; ++k) {
+            ar -= Lr[i][k] * ur[k] - Li[i][k] * ui[k];
+            ai -= Lr[i][k] * ui[k] + Li[i][k] * ur[k];
+        }
+        ur[i] = live[i] ? ar / Lr[i][i] : 0.0;
+        ui[i] = live[i] ? ai / Lr[i][i] : 0.0;
+    }
+#pragma unroll
+    for (int i = m - 1; i >= 0; --i) {   // L^H y = u
+        double ar = ur[i], ai = ui[i];
+#pragma unroll
+        for (int k = i + 1; k < m; ++k)
+            if (live[k]) {   // - conj(L_ki) y_k
+                ar -= Lr[k][i] * yr[k] + Li[k][i] * yi[k];
+                ai -= Lr[k][i] * yi[k] - Li[k][i] * yr[k];
+            }
+        yr[i] = live[i] ? ar / Lr[i][i] : 0.0;
+        yi[i] = live[i] ? ai / Lr[i][i] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < kMMax; ++j) {
+        st->y[j][0] = j < m ? yr[j < m ? j : 0] : 0.0;
+        st->y[j][1] = j < m ? yi[j < m ? j : 0] : 0.0;
+    }
+    if (!(tot[0].r == tot[0].r) || !(tot[0].r < 1e300)) st->nonfinite = 1;
+}
+
 // Gram matrix G_ij = <P_i, P_j> (i <= j) of the s-step basis P_0..P_{NP-1}, then
 // the least-squares coefficients y of min ||P_0 - [P_1..P_{NP-1}] y|| from the
 // normal equations by Cholesky (truncated at a vanishing pivot).
@@ -495,12 +655,19 @@ __global__ void __launch_bounds__(1024) k_gram(Ptrs<T, NP> P, long long n, KStat
                 ++s;
             }
     }
-    if (!reduce_partials<NS>(acc, rb)) return;
     __shared__ D2 tot[kSlots];
+    if (!reduce_partials<NS>(acc, rb, tot)) return;
     sum_partials<NS>(rb, tot);
-    // the small dense solve runs on one thread with its arrays in LDS
-    // (dynamically indexed arrays in registers would go to scratch memory)
     constexpr int m = NP - 1;
+    if constexpr (NP <= 5) {
+        if (threadIdx.x == 0) {
+            gram_solve<NP>(tot, st);
+            reset_ticket(rb.counter);
+        }
+        return;
+    }
+    // longer bases: the small dense solve runs on one thread with its arrays in LDS
+    // (dynamically indexed arrays in registers would go to scratch memory)
     __shared__ double G[NP][NP][2];
     __shared__ double Lr[m][m], Li[m][m], ur[m], ui[m];
     if (threadIdx.x == 0) {
