@@ -263,14 +263,15 @@ template <typename T>
 hipError_t launch_axpy_scale(const T *const *V, int nv, T *w, long long n, KState *st, hipStream_t s);
 
 
-// x (+)= sum_j y_j Z_j with y from the state: back substitution of the
-// rotated Hessenberg (from_backsolve) or the stored s-step coefficients.  With
+// x = base + sum_j y_j Z_j (base: x itself, another vector, or null for zero) with y from the
+// state: back substitution of the rotated Hessenberg (from_backsolve) or the stored s-step
+// coefficients.  With
 // c16 Z and a c32 / c64 x, Z_j is stored with the scale zf * qs_j, qs_0 = st->vs0
 // (the cycle's first basis vector kept unnormalised) and qs_j = 1 for j >= 1;
 // with c16 Z and c16 x both carry the same scale (no conversion).
 template <typename TX, typename TZ>
-hipError_t launch_combine(TX *x, const TZ *const *Z, int nz, long long n, KState *st, bool from_backsolve,
-                          bool overwrite, hipStream_t s, float zf = 1.0f);
+hipError_t launch_combine(TX *x, const TX *base, const TZ *const *Z, int nz, long long n, KState *st,
+                          bool from_backsolve, hipStream_t s, float zf = 1.0f);
 // y = x with the scales of c16 operands applied (true values in, true values out)
 template <typename TI, typename TO>
 hipError_t launch_convert_scaled(const TI *x, TO *y, long long n, Scale si, Scale so, hipStream_t s);

@@ -463,40 +463,56 @@ __global__ void __launch_bounds__(256) k_axpy_scale(Ptrs<T, NV> P, T *__restrict
 }
 
 // y = R^{-1} g: back substitution of the rotated Hessenberg over its kk columns
-// (guarded zero pivots), y_j = 0 beyond; one thread.
+// (guarded zero pivots), y_j = 0 beyond.  One wavefront: lane i keeps the running right-hand side
+// of row i; the columns are eliminated from the last one on, each with all rows at once.  The
+// matrix comes to LDS in one round of loads (one thread reading it from memory entry by
+// entry took 9 to 12 us).
 __global__ void __launch_bounds__(64) k_backsolve(KState *st, int nv, Batch bt) {
-    if (threadIdx.x != 0 || slot_off(bt, blockIdx.y)) return;
+    if (slot_off(bt, blockIdx.y)) return;
     st = slot_ptr(st, 1, blockIdx.y);
+    __shared__ double H[kMMax][kMMax][2];
+    const int lane = threadIdx.x;
+    for (int e = lane; e < kMMax * kMMax * 2; e += 64) (&H[0][0][0])[e] = (&st->H[0][0][0])[e];
     const int kk = st->kk < nv ? st->kk : nv;
-    for (int j = kk; j < kMMax; ++j) st->y[j][0] = st->y[j][1] = 0.0;
-    for (int i = kk - 1; i >= 0; --i) {
-        double sr = st->g[i][0], si = st->g[i][1];
-        for (int j = i + 1; j < kk; ++j) {
-            const double hr = st->H[i][j][0], hi = st->H[i][j][1];
-            sr -= hr * st->y[j][0] - hi * st->y[j][1];
-            si -= hr * st->y[j][1] + hi * st->y[j][0];
-        }
-        const double dr = st->H[i][i][0], di = st->H[i][i][1];
+    double sr = 0.0, si = 0.0, yr = 0.0, yi = 0.0;
+    if (lane < kk) {
+        sr = st->g[lane][0];
+        si = st->g[lane][1];
+    }
+    __syncthreads();
+    for (int j = kk - 1; j >= 0; --j) {
+        const double dr = H[j][j][0], di = H[j][j][1];
         const double d2 = dr * dr + di * di;
-        if (d2 == 0.0) {
-            st->y[i][0] = st->y[i][1] = 0.0;
-        } else {
-            st->y[i][0] = (sr * dr + si * di) / d2;
-            st->y[i][1] = (si * dr - sr * di) / d2;
+        const double gr = __shfl(sr, j, 64), gi = __shfl(si, j, 64);
+        const double xr = d2 == 0.0 ? 0.0 : (gr * dr + gi * di) / d2;
+        const double xi = d2 == 0.0 ? 0.0 : (gi * dr - gr * di) / d2;
+        if (lane == j) {
+            yr = xr;
+            yi = xi;
         }
+        if (lane < j) {
+            const double hr = H[lane][j][0], hi = H[lane][j][1];
+            sr -= hr * xr - hi * xi;
+            si -= hr * xi + hi * xr;
+        }
+    }
+    if (lane < kMMax) {
+        st->y[lane][0] = yr;
+        st->y[lane][1] = yi;
     }
 }
 
-// x (+)= sum_j y_j Z_j with y from st->y (written by k_backsolve or by the
-// s-step Gram solve)
+// x = base + sum_j y_j Z_j with y from st->y (written by k_backsolve or by the
+// s-step Gram solve); base may be x, or null for zero
 template <typename TX, typename TZ, int NV>
-__global__ void __launch_bounds__(256) k_combine(TX *__restrict__ x, Ptrs<TZ, NV> Zp, long long n, const KState *st,
-                                                int overwrite, float zf, Batch bt) {
+__global__ void __launch_bounds__(256) k_combine(TX *x, const TX *base, Ptrs<TZ, NV> Zp, long long n, const KState *st,
+                                                float zf, Batch bt) {
     const int sl = blockIdx.y;
     if (slot_off(bt, sl)) return;
 #pragma unroll
     for (int j = 0; j < NV; ++j) Zp.v[j] = slot_ptr(Zp.v[j], n, sl);
     x = slot_ptr(x, n, sl);
+    base = slot_ptr(base, n, sl);
     st = slot_ptr(st, 1, sl);
     using RA = std::conditional_t<is_half<TX>(), float, real_of<TX>>;   // FP16-stored x adds in FP32
     __shared__ double ys[NV][2];
@@ -520,8 +536,8 @@ __global__ void __launch_bounds__(256) k_combine(TX *__restrict__ x, Ptrs<TZ, NV
     const long long i = elem_index();
     if (i >= n) return;
     RA ar = 0, ai = 0;
-    if (!overwrite) {
-        const TX v = x[i];
+    if (base) {
+        const TX v = base[i];
         ar = (RA)v.re;
         ai = (RA)v.im;
     }
@@ -943,8 +959,8 @@ hipError_t launch_axpy_scale(const T *const *V, int nv, T *w, long long n, KStat
 }
 
 template <typename TX, typename TZ>
-hipError_t launch_combine(TX *x, const TZ *const *Z, int nz, long long n, KState *st, bool from_backsolve,
-                          bool overwrite, hipStream_t s, float zf) {
+hipError_t launch_combine(TX *x, const TX *base, const TZ *const *Z, int nz, long long n, KState *st,
+                          bool from_backsolve, hipStream_t s, float zf) {
     if (nz < 1 || nz > kMMax) return hipErrorInvalidValue;
     if (from_backsolve) {
         hipLaunchKernelGGL(k_backsolve, dim3(1, cur_batch().n), dim3(64), 0, s, st, nz, cur_batch());
@@ -954,8 +970,8 @@ hipError_t launch_combine(TX *x, const TZ *const *Z, int nz, long long n, KState
     const unsigned nb = stream_blocks(n);
 #define HELM_CB(NV)                                                                                            \
     case NV:                                                                                                   \
-        hipLaunchKernelGGL((k_combine<TX, TZ, NV>), dim3(nb, cur_batch().n), dim3(256), 0, s, x, pack<TZ, NV>(Z), n, st,       \
-                           (int)overwrite, zf, cur_batch());                                                                \
+        hipLaunchKernelGGL((k_combine<TX, TZ, NV>), dim3(nb, cur_batch().n), dim3(256), 0, s, x, base, pack<TZ, NV>(Z), n,     \
+                           st, zf, cur_batch());                                                                            \
         break;
     switch (nz) {
         HELM_CB(1) HELM_CB(2) HELM_CB(3) HELM_CB(4) HELM_CB(5) HELM_CB(6) HELM_CB(7) HELM_CB(8) HELM_CB(9)
@@ -1028,15 +1044,15 @@ hipError_t launch_velocity_check(const float *v, long long n, const RedBuf &rb, 
 HELM_INST(c32)
 HELM_INST(c64)
 #undef HELM_INST
-template hipError_t launch_combine<c32, c32>(c32 *, const c32 *const *, int, long long, KState *, bool, bool,
+template hipError_t launch_combine<c32, c32>(c32 *, const c32 *, const c32 *const *, int, long long, KState *, bool,
                                              hipStream_t, float);
-template hipError_t launch_combine<c64, c64>(c64 *, const c64 *const *, int, long long, KState *, bool, bool,
+template hipError_t launch_combine<c64, c64>(c64 *, const c64 *, const c64 *const *, int, long long, KState *, bool,
                                              hipStream_t, float);
-template hipError_t launch_combine<c64, c32>(c64 *, const c32 *const *, int, long long, KState *, bool, bool,
+template hipError_t launch_combine<c64, c32>(c64 *, const c64 *, const c32 *const *, int, long long, KState *, bool,
                                              hipStream_t, float);
-template hipError_t launch_combine<c32, c16>(c32 *, const c16 *const *, int, long long, KState *, bool, bool,
+template hipError_t launch_combine<c32, c16>(c32 *, const c32 *, const c16 *const *, int, long long, KState *, bool,
                                              hipStream_t, float);
-template hipError_t launch_combine<c16, c16>(c16 *, const c16 *const *, int, long long, KState *, bool, bool,
+template hipError_t launch_combine<c16, c16>(c16 *, const c16 *, const c16 *const *, int, long long, KState *, bool,
                                              hipStream_t, float);
 template hipError_t launch_gram<c16>(const c16 *const *, int, long long, KState *, const RedBuf &, hipStream_t);
 
