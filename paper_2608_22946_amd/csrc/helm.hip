@@ -74,8 +74,11 @@ struct helm_hierarchy {
     void *dinv[3][2];    // D^-1 of A_l and B_l per level, in the working precision
     float *wf[3][3];
     double *wd[3][3];
-    float *atab_f, *btab_f, *ctab_f;
+    float *atab_f, *btab_f;
     double *atab_d, *btab_d;
+    // per level, times ell^-2: the stencils' cubics (LevelArgs::etab) and, in the FP32 modes, the shell quintics
+    float *etab_f[3], *ctab_f[3];
+    double *etab_d[3];
     // HELM_MIXED: FP16-stored vectors hold v * f * qs (helm_internal.h), f = fres[l] for
     // residual-like vectors (the cycle input, residuals, the bottom basis P) and fsol[l]
     // for correction-like ones (Jacobi iterates, corrections, Z); d_one is the qs of
@@ -168,12 +171,17 @@ size_t carve(helm_hierarchy *H, char *base, const int N[3], const helm_options &
             Hp->wd[l][a] = c.take<double>(6 * (size_t)(g[l].n[a] + 1));
         }
     }
-    Hp->atab_f = c.take<float>(20 * (size_t)K);
-    Hp->btab_f = c.take<float>(12 * (size_t)K);
-    Hp->ctab_f = c.take<float>(24 * (size_t)(K + 1));
+    // the tables of each type back to back: one upload each
+    Hp->atab_f = c.take<float>((32 + 3 * 20) * (size_t)K + 3 * 24 * (size_t)(K + 1));
+    Hp->atab_d = c.take<double>((32 + 3 * 20) * (size_t)K);
+    Hp->btab_f = Hp->atab_f + 20 * (size_t)K;
+    Hp->btab_d = Hp->atab_d + 20 * (size_t)K;
+    for (int l = 0; l < 3; ++l) {
+        Hp->etab_f[l] = Hp->btab_f + (12 + 20 * l) * (size_t)K;
+        Hp->etab_d[l] = Hp->btab_d + (12 + 20 * l) * (size_t)K;
+        Hp->ctab_f[l] = Hp->btab_f + 72 * (size_t)K + 24 * l * (size_t)(K + 1);
+    }
     Hp->d_one = c.take<double>(1);
-    Hp->atab_d = c.take<double>(20 * (size_t)K);
-    Hp->btab_d = c.take<double>(12 * (size_t)K);
     const int nl = (o.lanes > 1) ? o.lanes : 1;
     if (H) H->nlanes = nl;
     for (int li = 0; li < nl; ++li) {
@@ -356,7 +364,9 @@ void fill_level_args(helm_hierarchy *H, int l, LevelArgs<R> &L, const R *wx, con
     for (int sh = 0; sh < 2; ++sh) L.dinv[sh] = own ? static_cast<const R *>(H->dinv[l][sh]) : nullptr;
     const bool fp32 = sizeof(R) == sizeof(float) && H->prec != HELM_FP64;
     L.s = fp32 ? H->svel[l] : nullptr;
-    L.ctab = fp32 ? reinterpret_cast<const R *>(H->ctab_f) : nullptr;
+    L.ctab = fp32 ? reinterpret_cast<const R *>(H->ctab_f[l]) : nullptr;
+    L.etab = sizeof(R) == sizeof(float) ? reinterpret_cast<const R *>(H->etab_f[l])
+                                        : reinterpret_cast<const R *>(H->etab_d[l]);
     L.kap_s = (R)(2.0 * M_PI * 0.4 / H->opt.iofd_K);
     // table window: the interval of a node is monotone in its velocity, so the velocity
     // range [cmin, cmax] bounds it; the same formulas as the kernels (locate / locate_s,
@@ -1253,22 +1263,30 @@ helm_status helm_setup(const float *velocity, int nx, int ny, int nz, double h, 
     hermite_monomials(opt->iofd_table, opt->iofd_K, 0, 5, at);
     hermite_monomials(opt->iofd_table, opt->iofd_K, 5, 3, bt);
     shell_quintics(at, opt->iofd_K, ct);
-    std::vector<float> atf(at.begin(), at.end()), btf(bt.begin(), bt.end()), ctf(ct.begin(), ct.end());
+    // alpha, beta, then per level the stencils' tables, scaled in FP64 and rounded once
+    std::vector<double> td(at);
+    td.insert(td.end(), bt.begin(), bt.end());
+    for (int l = 0; l < 3; ++l) {
+        const double inv = 1.0 / (H->geom[l].ell * H->geom[l].ell);
+        static const double part[5] = {1.0, 1.0 / 6, 1.0 / 12, 1.0, 1.0};
+        for (size_t i = 0; i < at.size(); ++i) td.push_back(at[i] * (part[i / 4 % 5] * inv));
+    }
+    std::vector<float> tf(td.begin(), td.end());
+    for (int l = 0; l < 3; ++l) {
+        const double inv = 1.0 / (H->geom[l].ell * H->geom[l].ell);
+        for (double v : ct) tf.push_back((float)(v * inv));
+    }
+    if ((e = hipMemcpyAsync(H->atab_d, td.data(), td.size() * sizeof(double), hipMemcpyHostToDevice, s)) != hipSuccess ||
+        (e = hipMemcpyAsync(H->atab_f, tf.data(), tf.size() * sizeof(float), hipMemcpyHostToDevice, s)) != hipSuccess)
+        return bail(HELM_EHIP, std::string("table upload: ") + hipGetErrorString(e));
     if (H->prec != HELM_FP64) {
-        if ((e = hipMemcpyAsync(H->ctab_f, ctf.data(), ctf.size() * sizeof(float), hipMemcpyHostToDevice, s)) !=
-            hipSuccess)
-            return bail(HELM_EHIP, std::string("table upload: ") + hipGetErrorString(e));
         for (int l = 0; l < 3; ++l) {
             const double factor = omega * H->geom[l].ell * opt->iofd_K / (0.4 * 2.0 * M_PI);
             if ((e = launch_scaled_eta(H->vel[l], H->geom[l].nn, factor, H->svel[l], s)) != hipSuccess)
                 return bail(HELM_EHIP, hipGetErrorString(e));
         }
     }
-    if ((e = hipMemcpyAsync(H->atab_d, at.data(), at.size() * sizeof(double), hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(H->btab_d, bt.data(), bt.size() * sizeof(double), hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(H->atab_f, atf.data(), atf.size() * sizeof(float), hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(H->btab_f, btf.data(), btf.size() * sizeof(float), hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
+    if ((e = hipStreamSynchronize(s)) != hipSuccess)   // the host tables go out of scope
         return bail(HELM_EHIP, std::string("table upload: ") + hipGetErrorString(e));
     for (int l = 0; l < 3; ++l) {
         // FP16 units: a cycle input of unit norm has entries of RMS 1/64; D^-1 ~ ell^2 / 4

@@ -125,7 +125,9 @@ struct LevelArgs {
     // quintics in the local coordinate t of each table interval, interval K standing for
     // the clamped range s >= K (t = s - K unbounded there).  Null in FP64 arguments.
     const float *s;
-    const R *ctab;       // [K + 1][4][6] monomial coefficients in t
+    const R *ctab;       // [K + 1][4][6] monomial coefficients in t, times ell^-2
+    // [K][5][4] cubics in t of a1, a2 / 6, a3 / 12, a4, a5, times ell^-2 (the level stencils' form)
+    const R *etab;
     R kap_s;             // kappa per unit of s: 0.4 * 2 pi / K
     // table intervals the stencils stage in LDS: the alpha pieces kb .. kb + nk - 1 and the
     // shell quintics cb .. cb + nck - 1, every interval a node of this level can reach

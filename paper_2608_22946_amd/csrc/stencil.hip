@@ -1,11 +1,12 @@
-// Level-operator kernels: instantiations for FP32 and FP64 operands, the operator
-// hooks (Q_h, diag, one Jacobi sweep) and D^-1 (the stencil itself is in stencil_impl.h).
+// Level-operator kernels: instantiations for FP32 operands, the operator hooks (Q_h, diag, one
+// Jacobi sweep) and D^-1 (the stencil itself is in stencil_impl.h).
 #include "stencil_impl.h"
 
 namespace helm {
 
+// upper bound over every tiling: the plain x tiles and a wavefront of edge strips a row
 int stencil_blocks(int nx, int ny, int nz, int tz) {
-    const int ntx = 1 + ceil_div(nx + 1, kTileX);   // upper bound for both x tilings
+    const int ntx = 2 + ceil_div(nx + 1, kTileX);
     const int nty = ceil_div(ny + 1, kWavesY);
     if (tz <= 0) tz = pick_tz(ntx, nty, nz + 1);
     return ntx * nty * ceil_div(nz + 1, tz);
@@ -58,10 +59,6 @@ template hipError_t launch_jac1<float, c32>(const LevelArgs<float> &, int, doubl
 template hipError_t launch_jac1<double, c64>(const LevelArgs<double> &, int, double, const c64 *, c64 *, hipStream_t);
 template hipError_t launch_stencil<float, c32, c32, c32>(const LevelArgs<float> &, const StencilCall &, const RedBuf &,
                                                          hipStream_t);
-template hipError_t launch_stencil<double, c64, c64, c64>(const LevelArgs<double> &, const StencilCall &,
-                                                          const RedBuf &, hipStream_t);
-template hipError_t launch_stencil<double, c64, c64, c32>(const LevelArgs<double> &, const StencilCall &,
-                                                          const RedBuf &, hipStream_t);
 template hipError_t launch_qapply<double, c32, c64>(const LevelArgs<double> &, const c32 *, c64 *, hipStream_t);
 template hipError_t launch_qapply<double, c64, c32>(const LevelArgs<double> &, const c64 *, c32 *, hipStream_t);
 template hipError_t launch_qapply<double, c64, c64>(const LevelArgs<double> &, const c64 *, c64 *, hipStream_t);

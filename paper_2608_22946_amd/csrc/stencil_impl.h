@@ -23,9 +23,21 @@
 // reciprocal, the clamped interpolation coordinate and five cubic polynomials
 // read from an LDS copy of the table, so the only per-node data read besides
 // the operand is the FP32 velocity.
+//
+// What bounds it.  On a large level the memory path of the march: halving the vector instructions
+// of its interior rows (124 -> 56 per plane) left the apply at 352^3 where it was (244 -> 245 us),
+// one, two or three planes in flight measure the same, and without its stores the same loads
+// take 108 us (67 us with one row load instead of three) of the 231 us that they take with
+// them; a linear stream of the same arrays takes 140 us.  On a coarse level, which the cache
+// holds, the instructions and the latency of a launch: there the shorter code is the gain (2h
+// level of a 352^3 grid: J2 42.2 -> 37.8 us, apply 32.0 -> 30.2 us; 4h: 12.5 -> 10.6 us,
+// 10.2 -> 8.4 us).  Measured and not kept: four rows a wavefront in registers (190 us for the
+// loads and stores alone, but 148 registers: apply 237 us, 2h apply 42 us), rows shared by
+// eight wavefronts through LDS with one barrier a plane (187 us alone, apply 260 us).
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
 
 #include "helm_internal.h"
 
@@ -56,22 +68,23 @@ __device__ __forceinline__ Z<R> zdiv(Z<R> a, Z<R> d) {
 }
 
 // value from the lane holding x-1 (wave_shr:1) and from the lane holding x+1 (wave_shl:1)
+// (lanes without a source read 0 by bound_ctrl, so the shift folds into the addition that uses it)
 __device__ __forceinline__ float from_left(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xf, 0xf, true));
 }
 __device__ __forceinline__ float from_right(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xf, 0xf, true));
 }
 __device__ __forceinline__ double from_left(double v) {
     long long b = __double_as_longlong(v);
-    int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), 0x138, 0xf, 0xf, false);
-    int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x138, 0xf, 0xf, false);
+    int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), 0x138, 0xf, 0xf, true);
+    int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x138, 0xf, 0xf, true);
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 __device__ __forceinline__ double from_right(double v) {
     long long b = __double_as_longlong(v);
-    int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), 0x130, 0xf, 0xf, false);
-    int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x130, 0xf, 0xf, false);
+    int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), 0x130, 0xf, 0xf, true);
+    int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x130, 0xf, 0xf, true);
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 template <typename R>
@@ -168,22 +181,94 @@ __device__ __forceinline__ Coef<R> coef_at(const LevelArgs<R> &L, const R *stab,
     return o;
 }
 
-// unshifted shell coefficients C_0..C_3 at a node of an FP32 level from the quintic table
-// (LDS copy `ctab`): interval min(floor(s), K), the last one unbounded in t
+// Coefficients of one row as the march uses them, all times ell^-2: mass weights m0..m3 =
+// (a1, a2 / 6, a3 / 12, (1 - a1 - a2 - a3) / 8), the transverse functions a4, a5 and
+// q = 1 - a4 - a5, and kappa^2.
 template <typename R>
-__device__ __forceinline__ void shell_at_s(const LevelArgs<R> &L, const R *ctab, float s, R &c0, R &c1, R &c2,
-                                           R &c3) {
-    int k = (int)s;
-    k = k < L.K ? k : L.K;
-    const R t = (R)s - (R)k;
-    // ctab holds the intervals cb .. cb + nck - 1 (the level's window)
-    const int kw = k < L.cb ? L.cb : (k > L.cb + L.nck - 1 ? L.cb + L.nck - 1 : k);
-    const R *p = ctab + (kw - L.cb) * 24;
-    c0 = horner5(p, t);
-    c1 = horner5(p + 6, t);
-    c2 = horner5(p + 12, t);
-    c3 = horner5(p + 18, t);
+struct RowCoef {
+    R m0, m1, m2, m3, a4, a5, q, k2;
+};
+
+// A table piece in LDS is read with 16-byte loads (ds_read_b128; the pieces are multiples of 16 B
+// from an aligned base): 24 floats of a node's quintics take 6 loads instead of 12.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+template <int N>
+__device__ __forceinline__ void lds_read(const float *p, float (&o)[N]) {
+    static_assert(N % 4 == 0, "whole 16-byte loads");
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) {
+        const f32x4 v = reinterpret_cast<const f32x4 *>(p)[i];
+        o[4 * i] = v.x; o[4 * i + 1] = v.y; o[4 * i + 2] = v.z; o[4 * i + 3] = v.w;
+    }
 }
+template <int N>
+__device__ __forceinline__ void lds_read(const double *p, double (&o)[N]) {
+    static_assert(N % 2 == 0, "whole 16-byte loads");
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+        const f64x2 v = reinterpret_cast<const f64x2 *>(p)[i];
+        o[2 * i] = v.x; o[2 * i + 1] = v.y;
+    }
+}
+// byte offset of table piece k (a small whole number held in a float) in a window that starts at
+// piece `first`: one multiply-add and a conversion (an integer multiply is quarter rate)
+__device__ __forceinline__ unsigned piece_offset(float k, float first, float bytes) {
+    return (unsigned)((k - first) * bytes);
+}
+
+// RowCoef from the level's scaled table (LDS copy `etab`); v as in coef_at
+__device__ __forceinline__ RowCoef<float> row_coef(const LevelArgs<float> &L, const float *etab, float v) {
+    const float u = fminf(v, (float)L.K);   // eta* clamped at 0.4
+    // the window holds every interval a node of the level reaches
+    const float k = __builtin_amdgcn_fmed3f(truncf(u), (float)L.kb, (float)(L.kb + L.nk - 1));
+    const float t = u - k;
+    float c[20];
+    lds_read(reinterpret_cast<const float *>(reinterpret_cast<const char *>(etab) +
+                                             piece_offset(k, (float)L.kb, 80.0f)), c);
+    RowCoef<float> o;
+    o.m0 = horner(c, t);
+    o.m1 = horner(c + 4, t);
+    o.m2 = horner(c + 8, t);
+    o.a4 = horner(c + 12, t);
+    o.a5 = horner(c + 16, t);
+    o.m3 = 0.125f * (L.inv_ell2 - o.m0) - 0.75f * o.m1 - 1.5f * o.m2;
+    o.q = L.inv_ell2 - o.a4 - o.a5;
+    const float kappa = v * L.kap_s;
+    o.k2 = kappa * kappa;
+    return o;
+}
+__device__ __forceinline__ RowCoef<double> row_coef(const LevelArgs<double> &L, const double *etab, float v) {
+    double kappa, t;
+    int k;
+    locate(L, v, kappa, k, t);
+    k = k < L.kb ? L.kb : (k > L.kb + L.nk - 1 ? L.kb + L.nk - 1 : k);
+    double c[20];
+    lds_read(etab + (k - L.kb) * 20, c);
+    RowCoef<double> o;
+    o.m0 = horner(c, t);
+    o.m1 = horner(c + 4, t);
+    o.m2 = horner(c + 8, t);
+    o.a4 = horner(c + 12, t);
+    o.a5 = horner(c + 16, t);
+    o.m3 = 0.125 * (L.inv_ell2 - o.m0) - 0.75 * o.m1 - 1.5 * o.m2;
+    o.q = L.inv_ell2 - o.a4 - o.a5;
+    o.k2 = kappa * kappa;
+    return o;
+}
+
+// unshifted shell coefficients C_0..C_3 (times ell^-2) at a node of an FP32 level from the quintic
+// table (LDS copy `ctab`): interval min(floor(s), K), the last one unbounded in t
+__device__ __forceinline__ void shell_coef(const LevelArgs<float> &L, const float *ctab, float s, float (&C)[4]) {
+    const float k = __builtin_amdgcn_fmed3f(truncf(s), (float)L.cb, (float)(L.cb + L.nck - 1));
+    const float t = s - k;
+    float c[24];
+    lds_read(reinterpret_cast<const float *>(reinterpret_cast<const char *>(ctab) +
+                                             piece_offset(k, (float)L.cb, 96.0f)), c);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) C[m] = horner5(c + 6 * m, t);
+}
+__device__ __forceinline__ void shell_coef(const LevelArgs<double> &, const double *, float, double (&)[4]) {}
 
 // per-node value a level's coefficient evaluation reads
 template <typename R>
@@ -204,150 +289,127 @@ template <typename R>
 struct Plane {
     Z<R> p0, p1, p2;   // centre, 4 in-plane face neighbours, 4 in-plane corners
     Z<R> ea, eb;       // x/y stiffness partials (tensor form only)
-    Z<R> gc;           // right-hand side at the centre (residual / Jacobi modes)
+    Z<R> gc;           // right-hand side at the centre (residual / sweep modes)
     Z<R> dc;           // D^-1 at the centre (Jacobi modes)
     Z<R> bc;           // base value at the centre (fused Jacobi + base)
     float cc;          // per-node value at the centre (s on FP32 levels, c on FP64 ones)
 };
 
+// w . (l, c, r) with complex weights
+template <typename R>
+__device__ __forceinline__ Z<R> wdot(const Z<R> (&w)[3], Z<R> l, Z<R> c, Z<R> r) {
+    return zfma(w[2], r, zfma(w[1], c, zmul(w[0], l)));
+}
+// 2 a - b
+template <typename R>
+__device__ __forceinline__ Z<R> twice_less(Z<R> a, Z<R> b) { return {(R)2 * a.r - b.r, (R)2 * a.i - b.i}; }
+
 // In-plane partial sums of one z plane from the rows y-1 (a), y (b), y+1 (c)
 // at this lane's x; x neighbours come from the adjacent lanes.  XI / YI: the
 // x / y stretching of this wave is the identity (weights -1, 2, -1).
 template <typename R, bool XI, bool YI>
-__device__ __forceinline__ void plane_partials(Z<R> a, Z<R> b, Z<R> c, const Z<R> *wx, const Z<R> *wy,
+__device__ __forceinline__ void plane_partials(Z<R> a, Z<R> b, Z<R> c, const Z<R> (&wx)[3], const Z<R> (&wy)[3],
                                                Plane<R> &P) {
     const Z<R> col = zadd(a, c);
-    const Z<R> bL = zleft(b), bR = zright(b);
     P.p0 = b;
-    if (XI && YI) {
-        P.p1 = zadd(col, zadd(bL, bR));
+    if constexpr (XI && YI) {
+        P.p1 = zadd(zadd(col, zleft(b)), zright(b));
         P.p2 = zadd(zleft(col), zright(col));
-        return;
-    }
-    const Z<R> aL = zleft(a), aR = zright(a), cL = zleft(c), cR = zright(c);
-    const Z<R> colL = zadd(aL, cL), colR = zadd(aR, cR);
-    const Z<R> rsm = zadd(aL, aR), rs0 = zadd(bL, bR), rsp = zadd(cL, cR);
-    P.p1 = zadd(col, rs0);
-    P.p2 = zadd(rsm, rsp);
-    Z<R> ea, eb;
-    if (XI) {            // -1, 2, -1 along x
-        ea = zsub(zscale((R)2, b), rs0);
-        eb = zsub(zscale((R)2, col), zadd(colL, colR));
+    } else if constexpr (YI) {   // x stretched, -1, 2, -1 along y
+        const Z<R> bL = zleft(b), bR = zright(b), colL = zleft(col), colR = zright(col);
+        const Z<R> rs0 = zadd(bL, bR);
+        P.p1 = zadd(col, rs0);
+        P.p2 = zadd(colL, colR);
+        P.ea = zadd(wdot(wx, bL, b, bR), twice_less(b, col));
+        P.eb = zadd(wdot(wx, colL, col, colR), twice_less(rs0, P.p2));
     } else {
-        ea = zmul(wx[0], bL);
-        ea = zfma(wx[1], b, ea);
-        ea = zfma(wx[2], bR, ea);
-        eb = zmul(wx[0], colL);
-        eb = zfma(wx[1], col, eb);
-        eb = zfma(wx[2], colR, eb);
+        const Z<R> rsm = zadd(zleft(a), zright(a)), rsp = zadd(zleft(c), zright(c));
+        const Z<R> bL = zleft(b), bR = zright(b);
+        const Z<R> rs0 = zadd(bL, bR);
+        P.p1 = zadd(col, rs0);
+        P.p2 = zadd(rsm, rsp);
+        if constexpr (XI) {      // -1, 2, -1 along x, y stretched
+            P.ea = zadd(wdot(wy, a, b, c), twice_less(b, rs0));
+            P.eb = zadd(wdot(wy, rsm, rs0, rsp), twice_less(col, P.p2));
+        } else {
+            P.ea = zadd(wdot(wx, bL, b, bR), wdot(wy, a, b, c));
+            P.eb = zadd(wdot(wx, zleft(col), col, zright(col)), wdot(wy, rsm, rs0, rsp));
+        }
     }
-    if (YI) {            // -1, 2, -1 along y
-        ea = zadd(ea, zsub(zscale((R)2, b), col));
-        eb = zadd(eb, zsub(zscale((R)2, rs0), zadd(rsm, rsp)));
-    } else {
-        ea = zfma(wy[0], a, ea);
-        ea = zfma(wy[1], b, ea);
-        ea = zfma(wy[2], c, ea);
-        eb = zfma(wy[0], rsm, eb);
-        eb = zfma(wy[1], rs0, eb);
-        eb = zfma(wy[2], rsp, eb);
-    }
-    P.ea = ea;
-    P.eb = eb;
+}
+
+// sum_m C_m S_m over the shell sums S_m of the 1 / 6 / 12 / 8 neighbours
+template <typename R>
+__device__ __forceinline__ Z<R> shell_sum(const R (&C)[4], const Z<R> (&S)[4]) {
+    return {C[0] * S[0].r + C[1] * S[1].r + C[2] * S[2].r + C[3] * S[3].r,
+            C[0] * S[0].i + C[1] * S[1].i + C[2] * S[2].i + C[3] * S[3].i};
 }
 
 // H v at the centre of plane "o" from planes m (z-1), o (z), p (z+1); the row's coefficients
-// come from the per-node value o.cc (s or c).  Unshifted rows of an FP32 level free of
-// stretching take the shell coefficients from the quintic table (one Horner per
-// coefficient); every other row evaluates alpha_1..alpha_5 (eq. iofd-shell-coefficients,
-// or the tensor-product form in the PML).
-template <typename R, bool XYI, bool SHIFT>
-__device__ __forceinline__ Z<R> row_value(const LevelArgs<R> &L, const R *stab, const R *ctab, const Plane<R> &m,
-                                          const Plane<R> &o, const Plane<R> &p, bool zint, const Z<R> *wz) {
-    // shell sums S_m over the 1 / 6 / 12 / 8 neighbours
-    const Z<R> S0 = o.p0;
-    const Z<R> S1 = zadd(o.p1, zadd(m.p0, p.p0));
-    const Z<R> S2 = zadd(o.p2, zadd(m.p1, p.p1));
-    const Z<R> S3 = zadd(m.p2, p.p2);
-    if (scaled_coordinate<R>() && !SHIFT && XYI && zint) {
-        R c0, c1, c2, c3;
-        shell_at_s(L, ctab, o.cc, c0, c1, c2, c3);
-        Z<R> out;
-        out.r = c0 * S0.r + c1 * S1.r + c2 * S2.r + c3 * S3.r;
-        out.i = c0 * S0.i + c1 * S1.i + c2 * S2.i + c3 * S3.i;
-        return zscale(L.inv_ell2, out);
-    }
-    const Coef<R> cf = coef_at(L, stab, o.cc);
-    const R a1 = cf.a1, a2 = cf.a2, a3 = cf.a3, a4 = cf.a4, a5 = cf.a5;
-    const R q = (R)1 - a4 - a5;
-    const R m0 = a1, m1 = a2 * (R)(1.0 / 6), m2 = a3 * (R)(1.0 / 12), m3 = ((R)1 - a1 - a2 - a3) * (R)0.125;
-    if (XYI && zint) {
-        // eq. iofd-shell-coefficients: C_m = stiffness_m - mu kappa^2 mass_m, then sum_m C_m S_m
-        const R k2 = cf.k2;
-        const R c0 = (R)6 * a4 - k2 * m0, c1 = (a5 - a4) - k2 * m1, c2 = (R)0.5 * (q - a5) - k2 * m2,
-                c3 = (R)-0.75 * q - k2 * m3;
-        Z<R> out;
-        out.r = c0 * S0.r + c1 * S1.r + c2 * S2.r + c3 * S3.r;
-        out.i = c0 * S0.i + c1 * S1.i + c2 * S2.i + c3 * S3.i;
-        if (SHIFT) {   // - i sigma kappa^2 sum_m mass_m S_m
-            const R sk = L.sigma * k2;
-            const R mr = m0 * S0.r + m1 * S1.r + m2 * S2.r + m3 * S3.r;
-            const R mi = m0 * S0.i + m1 * S1.i + m2 * S2.i + m3 * S3.i;
-            out.r += sk * mi;
-            out.i -= sk * mr;
-        }
-        return zscale(L.inv_ell2, out);
-    }
-    Z<R> Mass = zscale(m0, S0);
-    Mass = zadd(Mass, zscale(m1, S1));
-    Mass = zadd(Mass, zscale(m2, S2));
-    Mass = zadd(Mass, zscale(m3, S3));
-    Z<R> St;
-    {
-        const R t0 = a4, t1 = a5 * (R)0.25, t2 = q * (R)0.25;
-        Z<R> eam, ebm, eao, ebo, eap, ebp;
-        if (XYI) {   // unit x/y stretching: Ea = 4 P0 - P1, Eb = 2 P1 - 2 P2
-            eam = zsub(zscale((R)4, m.p0), m.p1);
-            ebm = zscale((R)2, zsub(m.p1, m.p2));
-            eao = zsub(zscale((R)4, o.p0), o.p1);
-            ebo = zscale((R)2, zsub(o.p1, o.p2));
-            eap = zsub(zscale((R)4, p.p0), p.p1);
-            ebp = zscale((R)2, zsub(p.p1, p.p2));
+// come from the per-node value o.cc (s or c).  Rows free of stretching take the shell form
+// (eq. iofd-shell-form): the unshifted ones of an FP32 level from the quintic table (one
+// Horner per coefficient), the others from alpha_1..alpha_5 (eq. iofd-shell-coefficients);
+// rows in the PML take the tensor-product form.  INNER: the row is known to be free of
+// stretching; otherwise zint says whether z is, and wzp holds the plane's z weights.
+template <typename R, bool XYI, bool SHIFT, bool INNER>
+__device__ __forceinline__ Z<R> row_value(const LevelArgs<R> &L, const R *etab, const R *ctab, const Plane<R> &m,
+                                          const Plane<R> &o, const Plane<R> &p, bool zint, const R *wzp) {
+    const Z<R> s0 = zadd(m.p0, p.p0), s1 = zadd(m.p1, p.p1), s2 = zadd(m.p2, p.p2);
+    const Z<R> S[4] = {o.p0, zadd(o.p1, s0), zadd(o.p2, s1), s2};
+    if (INNER || (XYI && zint)) {
+        if constexpr (scaled_coordinate<R>() && !SHIFT) {
+            R C[4];
+            shell_coef(L, ctab, o.cc, C);
+            return shell_sum(C, S);
         } else {
-            eam = m.ea; ebm = m.eb; eao = o.ea; ebo = o.eb; eap = p.ea; ebp = p.eb;
+            // C_m = stiffness_m - mu kappa^2 mass_m
+            const RowCoef<R> f = row_coef(L, etab, o.cc);
+            const R M[4] = {f.m0, f.m1, f.m2, f.m3};
+            const R C[4] = {(R)6 * f.a4 - f.k2 * f.m0, (f.a5 - f.a4) - f.k2 * f.m1,
+                            (R)0.5 * (f.q - f.a5) - f.k2 * f.m2, (R)-0.75 * f.q - f.k2 * f.m3};
+            Z<R> out = shell_sum(C, S);
+            if (SHIFT) {   // - i sigma kappa^2 sum_m mass_m S_m
+                const R sk = L.sigma * f.k2;
+                const Z<R> mass = shell_sum(M, S);
+                out.r += sk * mass.i;
+                out.i -= sk * mass.r;
+            }
+            return out;
         }
-        St = zscale(t0, eao);
-        St = zadd(St, zscale(t1, zadd(ebo, zadd(eam, eap))));
-        St = zadd(St, zscale(t2, zadd(ebm, ebp)));
-        // z-direction second difference with transverse weights
-        Z<R> z0, z1, z2;
-        if (zint) {   // unit z stretching: -1, 2, -1
-            z0 = zsub(zscale((R)2, o.p0), zadd(m.p0, p.p0));
-            z1 = zsub(zscale((R)2, o.p1), zadd(m.p1, p.p1));
-            z2 = zsub(zscale((R)2, o.p2), zadd(m.p2, p.p2));
-        } else {
-            z0 = zmul(wz[1], o.p0);
-            z0 = zfma(wz[0], m.p0, z0);
-            z0 = zfma(wz[2], p.p0, z0);
-            z1 = zmul(wz[1], o.p1);
-            z1 = zfma(wz[0], m.p1, z1);
-            z1 = zfma(wz[2], p.p1, z1);
-            z2 = zmul(wz[1], o.p2);
-            z2 = zfma(wz[0], m.p2, z2);
-            z2 = zfma(wz[2], p.p2, z2);
-        }
-        St = zadd(St, zscale(t0, z0));
-        St = zadd(St, zscale(t1, z1));
-        St = zadd(St, zscale(t2, z2));
     }
-    Z<R> out;
-    out.r = St.r - cf.k2 * Mass.r;
-    out.i = St.i - cf.k2 * Mass.i;
-    if (SHIFT) {   // - i sigma kappa^2 Mass
-        out.r += L.sigma * cf.k2 * Mass.i;
-        out.i -= L.sigma * cf.k2 * Mass.r;
+    const RowCoef<R> f = row_coef(L, etab, o.cc);
+    const R M[4] = {f.m0, f.m1, f.m2, f.m3};
+    const Z<R> mass = shell_sum(M, S);
+    // the x/y parts A0, A1, A2 of the transverse weights a4, a5 / 4, q / 4
+    Z<R> A0, A1, A2;
+    if constexpr (XYI) {   // unit x/y stretching: ea = 4 P0 - P1, eb = 2 P1 - 2 P2
+        A0 = {(R)4 * o.p0.r - o.p1.r, (R)4 * o.p0.i - o.p1.i};
+        A1 = {(R)2 * (o.p1.r - o.p2.r) + ((R)4 * s0.r - s1.r), (R)2 * (o.p1.i - o.p2.i) + ((R)4 * s0.i - s1.i)};
+        A2 = {(R)2 * (s1.r - s2.r), (R)2 * (s1.i - s2.i)};
+    } else {
+        A0 = o.ea;
+        A1 = zadd(o.eb, zadd(m.ea, p.ea));
+        A2 = zadd(m.eb, p.eb);
     }
-    return zscale(L.inv_ell2, out);
+    if (zint) {   // -1, 2, -1 along z
+        A0 = zadd(A0, twice_less(o.p0, s0));
+        A1 = zadd(A1, twice_less(o.p1, s1));
+        A2 = zadd(A2, twice_less(o.p2, s2));
+    } else {
+        const Z<R> wz[3] = {{wzp[0], wzp[1]}, {wzp[2], wzp[3]}, {wzp[4], wzp[5]}};
+        A0 = zadd(A0, wdot(wz, m.p0, o.p0, p.p0));
+        A1 = zadd(A1, wdot(wz, m.p1, o.p1, p.p1));
+        A2 = zadd(A2, wdot(wz, m.p2, o.p2, p.p2));
+    }
+    const R t1 = (R)0.25 * f.a5, t2 = (R)0.25 * f.q;
+    Z<R> out = {f.a4 * A0.r + t1 * A1.r + t2 * A2.r - f.k2 * mass.r,
+                f.a4 * A0.i + t1 * A1.i + t2 * A2.i - f.k2 * mass.i};
+    if (SHIFT) {   // - i sigma kappa^2 mass
+        const R sk = L.sigma * f.k2;
+        out.r += sk * mass.i;
+        out.i -= sk * mass.r;
+    }
+    return out;
 }
 
 __device__ __forceinline__ void block_reduce_store(double v, double *dst) {
@@ -398,42 +460,58 @@ __device__ void norm_epilogue(const RedBuf &rb, int nblocks, KState *st) {
     }
 }
 
-// Stencil outputs are stored with the non-temporal hint: the fine-level apply at 352^3 ran
-// 3% faster (0.279 -> 0.271 ms) with the solve unchanged.  Choosing the hint per level at
-// run time made every stencil slower (code generation of the march), so it is unconditional.
-__device__ __forceinline__ void st_nt(c32 *p, c32 v) {
-    const long long b = ((long long)__float_as_int(v.im) << 32) | (unsigned)__float_as_int(v.re);
-    __builtin_nontemporal_store(b, reinterpret_cast<long long *>(p));
-}
-__device__ __forceinline__ void st_nt(c64 *p, c64 v) {
-    __builtin_nontemporal_store(v.re, &p->re);
-    __builtin_nontemporal_store(v.im, &p->im);
-}
-__device__ __forceinline__ void st_nt(c16 *p, c16 v) {
-    const unsigned b = (unsigned)__builtin_bit_cast(unsigned short, v.re) |
-                       ((unsigned)__builtin_bit_cast(unsigned short, v.im) << 16);
-    __builtin_nontemporal_store(b, reinterpret_cast<unsigned *>(p));
-}
-
+// Loads and stores go through a buffer descriptor of the plane (scalar registers) with the row's
+// offset in a scalar register and the lane's byte offset in the row in a vector register, so that
+// no address arithmetic runs on the vector unit.  Stores of lanes without an output are dropped
+// by the descriptor's bound (their offset is kNoStore) instead of by a branch.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+constexpr unsigned kNoStore = 0xffffff00u;   // past every plane (at most 4097^2 nodes of 16 B)
 template <typename T>
-__device__ __forceinline__ const T *plane_ptr(const T *base, long long plane_stride, int z) {
-    return base + (long long)z * plane_stride;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_buf(const T *plane, unsigned nodes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(plane), 0, nodes * (unsigned)sizeof(T), 0x00020000);
 }
 template <typename T>
-__device__ __forceinline__ T at_byte(const T *plane, unsigned off) {
-    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(plane) + off);
+__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t b, unsigned lane_off, unsigned row_off) {
+    if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, lane_off, row_off, 0));
+    else if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b, lane_off, row_off, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(b, lane_off, row_off, 0));
+}
+template <typename T>
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t b, unsigned lane_off, unsigned row_off, T v) {
+    if constexpr (sizeof(T) == 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, lane_off, row_off, 0);
+    else if constexpr (sizeof(T) == 8)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, lane_off, row_off, 0);
+    else {
+        // 16 bytes go out as two stores: a store of more than 8 bytes reads its data registers
+        // late, and with the row offset in a scalar register the compiler puts no wait state
+        // before the next vector write to them.  The fused norm's squares, formed in the same
+        // registers, then reached memory in place of the imaginary part.
+        const u32x4 w = __builtin_bit_cast(u32x4, v);
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{w.x, w.y}, b, lane_off, row_off, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{w.z, w.w}, b, lane_off + 8u, row_off, 0);
+    }
 }
 
 // One wavefront: rows y-1, y, y+1 at 64 consecutive x, marching planes z0..z1-1.
 // Every load reads an in-bounds node (indices clamped to the grid) and
 // boundary / out-of-box values are masked to zero afterwards, so the loads
 // carry no branches; the per-lane byte offsets inside a plane are fixed and the
-// plane base is wave-uniform (scalar registers).
-template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, bool XI, bool YI>
-__device__ __forceinline__ void march(const LevelArgs<R> &L, const R *stab, const TX *__restrict__ x,
+// plane base is wave-uniform (scalar registers).  INNER: every plane and row the wave reads
+// lies inside the box and every row it forms is free of stretching, so nothing is masked
+// and one coefficient form remains; most waves of a large level are of this kind.
+template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, bool XI, bool YI,
+          bool INNER>
+__device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, const R *ctab, const TX *__restrict__ x,
                                       const TG *__restrict__ g, const TY *__restrict__ base, TY *__restrict__ y,
                                       R omegaJ, const R (&mul)[4], int xg, int yg, int z0, int z1, bool out_lane,
                                       double &nrm, int Z0 = 0) {
+    static_assert(!INNER || (XI && YI), "inner tiles have no stretching");
     // mul: multipliers of the c16 operands (x, g, base loads; y store), 1 for the others
     const R mx = mul[0], mg = mul[1], mb = mul[2], my = mul[3];
     constexpr bool JAC = (MODE == M_JAC2 || MODE == M_JAC2_ADD);
@@ -441,96 +519,94 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *stab, cons
     constexpr bool NEED_G = (MODE != M_APPLY);
     const bool x_int = (xg >= 1 && xg <= L.nx - 1);
     const int xc = min(max(xg, 0), L.nx);
-    const int ym = max(yg - 1, 0), yp = min(yg + 1, L.ny);
-    const unsigned e0 = (unsigned)(yg * (int)L.sx + xc), em = (unsigned)(ym * (int)L.sx + xc),
-                   ep = (unsigned)(yp * (int)L.sx + xc);
-    const unsigned bx0 = e0 * sizeof(TX), bxm = em * sizeof(TX), bxp = ep * sizeof(TX);
-    const unsigned bg0 = e0 * sizeof(TG), bgm = em * sizeof(TG), bgp = ep * sizeof(TG);
-    const unsigned bc0 = e0 * 4u;
+    const int ym = max(yg - 1, 0), yc = min(yg, L.ny), yp = min(yg + 1, L.ny);
+    // node offsets: of the lane in a row (vector), of the three rows in a plane (scalar where the
+    // wavefront has one row)
+    const unsigned lx = (unsigned)xc, r0 = (unsigned)(yc * (int)L.sx), rm = (unsigned)(ym * (int)L.sx),
+                   rp = (unsigned)(yp * (int)L.sx);
+    auto load_row = [&](const auto *p, unsigned ro) {
+        using E = std::remove_const_t<std::remove_reference_t<decltype(*p)>>;
+        if constexpr (XI)
+            return buf_load<E>(plane_buf(p, (unsigned)L.sy), lx * (unsigned)sizeof(E), ro * (unsigned)sizeof(E));
+        else
+            return buf_load<E>(plane_buf(p, (unsigned)L.sy), (ro + lx) * (unsigned)sizeof(E), 0);
+    };
     const bool rm_ok = x_int && (yg - 1 >= 1);
     const bool r0_ok = x_int && (yg >= 1) && (yg <= L.ny - 1);
     const bool rp_ok = x_int && (yg + 1 <= L.ny - 1);
 
     Z<R> wx[3] = {{0, 0}, {0, 0}, {0, 0}}, wy[3] = {{0, 0}, {0, 0}, {0, 0}};
-    {
+    if constexpr (!XI) {
         const R *w = L.wx + 6 * xc;
         wx[0] = {w[0], w[1]}; wx[1] = {w[2], w[3]}; wx[2] = {w[4], w[5]};
-        const R *v = L.wy + 6 * yg;
+    }
+    if constexpr (!YI) {
+        const R *v = L.wy + 6 * yc;
         wy[0] = {v[0], v[1]}; wy[1] = {v[2], v[3]}; wy[2] = {v[4], v[5]};
     }
     const Z<R> zero = {0, 0};
 
-    // Raw loads of one plane (issued one plane ahead of their use).
+    // Raw loads of one plane.
     using DT = cplx<R>;
     struct Raw {
-        TX va, vb, vc;     // operand rows (or the right-hand side rows in the Jacobi modes)
-        TG gb;             // right-hand side at the centre
+        TX va, vb, vc;     // operand rows (not in the Jacobi modes)
+        TG ga, gb, gc;     // right-hand side rows (Jacobi modes; gb alone in the others)
         DT da, db, dc;     // D^-1 rows (Jacobi modes; db alone in the sweep mode)
         TY bb;             // base at the centre (fused Jacobi + base)
-        float cb;          // velocity at the centre
-        int zp;
+        float cb;          // per-node coefficient value at the centre
     };
     constexpr bool SWEEP = (MODE == M_JSWEEP);
     const DT *dinv = reinterpret_cast<const DT *>(L.dinv[SHIFT ? 1 : 0]);
-    const unsigned bd0 = e0 * (unsigned)sizeof(DT), bdm = em * (unsigned)sizeof(DT), bdp = ep * (unsigned)sizeof(DT);
     // Planes past the tile's last plane z1 are re-read from z1 (a cache hit):
     // the prefetch is then issued unconditionally, which keeps the count of
     // outstanding loads the same on every path through the loop, so waiting
     // for one plane never waits for the planes issued after it.
     const int zlast = min(z1, L.nz);
     const float *vnode = node_values(L);
+    const unsigned sy = (unsigned)L.sy;   // (N + 1)^2 nodes of a plane, at most 4097^2
     auto issue = [&](int zp, Raw &r) {
-        const int zc = min(max(zp, 0), zlast);
-        r.zp = zp;
-        const float *cp = plane_ptr(vnode, L.sy, zc);
-        r.cb = at_byte(cp, bc0);
+        const unsigned long long po = (unsigned long long)(unsigned)min(max(zp, 0), zlast) * sy;
+        auto row = [&](const auto *p, unsigned ro) { return load_row(p + po, ro); };
         if constexpr (!JAC) {
-            const TX *xp = plane_ptr(x, L.sy, zc);
-            r.va = at_byte(xp, bxm);
-            r.vb = at_byte(xp, bx0);
-            r.vc = at_byte(xp, bxp);
-            if (NEED_G) r.gb = at_byte(plane_ptr(g, L.sy, zc), bg0);
-            if (SWEEP) r.db = at_byte(plane_ptr(dinv, L.sy, zc), bd0);
+            r.va = row(x, rm);
+            r.vb = row(x, r0);
+            r.vc = row(x, rp);
+            if constexpr (NEED_G) r.gb = row(g, r0);
+            if constexpr (SWEEP) r.db = row(dinv, r0);
         } else {
-            const TG *gp = plane_ptr(g, L.sy, zc);
-            r.va = at_byte(gp, bgm);
-            r.vb = at_byte(gp, bg0);
-            r.vc = at_byte(gp, bgp);
-            const DT *dp = plane_ptr(dinv, L.sy, zc);
-            r.da = at_byte(dp, bdm);
-            r.db = at_byte(dp, bd0);
-            r.dc = at_byte(dp, bdp);
-            if (MODE == M_JAC2_ADD) r.bb = at_byte(plane_ptr(base, L.sy, zc), e0 * (unsigned)sizeof(TY));
+            r.ga = row(g, rm);
+            r.gb = row(g, r0);
+            r.gc = row(g, rp);
+            r.da = row(dinv, rm);
+            r.db = row(dinv, r0);
+            r.dc = row(dinv, rp);
+            if constexpr (MODE == M_JAC2_ADD) r.bb = row(base, r0);
         }
+        r.cb = row(vnode, r0);
     };
     // mask boundary / out-of-box values and form the plane partials
-    auto finish = [&](const Raw &r, Plane<R> &P) {
-        const int zp = r.zp;
-        const bool zok = (zp >= 1 && zp <= L.nz - 1);
+    auto finish = [&](int zp, const Raw &r, Plane<R> &P) {
         Z<R> a, b, c;
-        Z<R> gc = zero;
         if constexpr (!JAC) {
             a = dq<R>(r.va, mx);
             b = dq<R>(r.vb, mx);
             c = dq<R>(r.vc, mx);
-            if (NEED_G) gc = dq<R>(r.gb, mg);
+            if constexpr (NEED_G) P.gc = dq<R>(r.gb, mg);
         } else {
-            a = dq<R>(r.va, mg);   // the loaded rows are g
-            b = dq<R>(r.vb, mg);
-            c = dq<R>(r.vc, mg);
-            // fused two-sweep Jacobi: the operand is y1 = omega D^-1 g at every loaded node
-            gc = b;
-            a = zscale(omegaJ, zmul(Z<R>{r.da.re, r.da.im}, a));
-            b = zscale(omegaJ, zmul(Z<R>{r.db.re, r.db.im}, b));
-            c = zscale(omegaJ, zmul(Z<R>{r.dc.re, r.dc.im}, c));
+            // fused two-sweep Jacobi: the operand is t = D^-1 g at every loaded node
+            a = zmul(Z<R>{r.da.re, r.da.im}, dq<R>(r.ga, mg));
+            b = zmul(Z<R>{r.db.re, r.db.im}, dq<R>(r.gb, mg));
+            c = zmul(Z<R>{r.dc.re, r.dc.im}, dq<R>(r.gc, mg));
         }
-        if (!(zok && rm_ok)) a = zero;
-        if (!(zok && r0_ok)) b = zero;
-        if (!(zok && rp_ok)) c = zero;
+        if constexpr (!INNER) {
+            const bool zok = (zp >= 1 && zp <= L.nz - 1);
+            if (!(zok && rm_ok)) a = zero;
+            if (!(zok && r0_ok)) b = zero;
+            if (!(zok && rp_ok)) c = zero;
+        }
         P.cc = r.cb;
-        P.gc = gc;
-        if (JAC || SWEEP) P.dc = Z<R>{r.db.re, r.db.im};
-        if (MODE == M_JAC2_ADD) P.bc = dq<R>(r.bb, mb);
+        if constexpr (JAC || SWEEP) P.dc = Z<R>{r.db.re, r.db.im};
+        if constexpr (MODE == M_JAC2_ADD) P.bc = dq<R>(r.bb, mb);
         plane_partials<R, XI, YI>(a, b, c, wx, wy, P);
     };
 
@@ -541,24 +617,28 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *stab, cons
     const int lane = threadIdx.x;
     const bool rstore = RESTRICT && (lane & 1) && lane >= 3 && lane <= 61 && yint && (xg >> 1) >= 1 && (xg >> 1) <= nxc - 1;
     Z<R> rcur = zero;
+    const unsigned store_off = out_lane ? (XI ? lx : r0 + lx) * (unsigned)sizeof(TY) : kNoStore;
+    const R omega2 = (R)2 * omegaJ, omegasq = omegaJ * omegaJ;
     // output plane z from planes m, o, p
     auto emit = [&](int z, const Plane<R> &m, const Plane<R> &o, const Plane<R> &p) {
-        Z<R> res = zero;
-        const bool interior = x_int && yint && z >= 1 && z <= L.nz - 1;
-        if (interior) {
-            const bool zint = (z >= L.loz && z <= L.hiz);
-            const R *wzp = L.wz + 6 * z;
-            const Z<R> wz[3] = {{wzp[0], wzp[1]}, {wzp[2], wzp[3]}, {wzp[4], wzp[5]}};
-            const Z<R> Hv = row_value<R, XI && YI, SHIFT>(L, stab, stab + 20 * L.nk, m, o, p, zint, wz);
-            if (MODE == M_APPLY) {
-                res = Hv;
-            } else if (MODE == M_RESID || RESTRICT) {
-                res = zsub(o.gc, Hv);
-            } else {
-                res = zadd(o.p0, zscale(omegaJ, zmul(o.dc, zsub(o.gc, Hv))));   // p0: operand / y1
-            }
+        const bool zint = INNER || (z >= L.loz && z <= L.hiz);
+        const Z<R> Hv = row_value<R, XI && YI, SHIFT, INNER>(L, etab, ctab, m, o, p, zint, L.wz + 6 * z);
+        Z<R> res;
+        if constexpr (MODE == M_APPLY) {
+            res = Hv;
+        } else if constexpr (MODE == M_RESID || RESTRICT) {
+            res = zsub(o.gc, Hv);
+        } else if constexpr (SWEEP) {
+            res = zadd(o.p0, zscale(omegaJ, zmul(o.dc, zsub(o.gc, Hv))));
+        } else {
+            // omega t + omega D^-1 (g - omega H t) with D^-1 g = t: neither g nor omega t is kept
+            const Z<R> dh = zmul(o.dc, Hv);
+            res = {omega2 * o.p0.r - omegasq * dh.r, omega2 * o.p0.i - omegasq * dh.i};
         }
-        if (RESTRICT) {
+        if constexpr (!INNER) {
+            if (!(r0_ok && z >= 1 && z <= L.nz - 1)) res = zero;
+        }
+        if constexpr (RESTRICT) {
             // full weighting along x (this lane's fine x is even on the storing
             // lanes) and along z (running sums over the coarse planes), stored per
             // fine row; the y weights follow in a second pass
@@ -575,37 +655,40 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *stab, cons
                 rcur.r += (R)0.5 * rx.r;
                 rcur.i += (R)0.5 * rx.i;
             }
-            return;
-        }
-        TY *yp_ = const_cast<TY *>(plane_ptr(y, L.sy, z));
-        if (MODE == M_JAC2_ADD) {
-            res.r += o.bc.r;
-            res.i += o.bc.i;
-        }
-        if (out_lane) {
-            st_nt(reinterpret_cast<TY *>(reinterpret_cast<char *>(yp_) + e0 * (unsigned)sizeof(TY)), qz<TY>(res, my));
-            if (NORM) nrm += (double)res.r * (double)res.r + (double)res.i * (double)res.i;
+        } else {
+            if constexpr (MODE == M_JAC2_ADD) {
+                res.r += o.bc.r;
+                res.i += o.bc.i;
+            }
+            buf_store(plane_buf(y + (unsigned long long)(unsigned)z * sy, sy), store_off,
+                      XI ? r0 * (unsigned)sizeof(TY) : 0u, qz<TY>(res, my));
+            if constexpr (NORM) {
+                if (out_lane) nrm += (double)res.r * (double)res.r + (double)res.i * (double)res.i;
+            }
         }
     };
 
-    // Two planes of loads stay in flight: a step issues plane z+3, forms the
-    // output of plane z, then turns the already-arrived plane z+2 into partial
-    // sums.  Plane slots rotate with period 3 and load buffers with period 2.
+    // The first three planes are loaded at once; then two planes of loads stay in flight: a
+    // step issues plane z+3, forms the output of plane z, then turns the already-arrived plane
+    // z+2 into partial sums.  Plane slots rotate with period 3 and load buffers with period 2.
     Plane<R> P0, P1, P2;
     Raw ra, rb;
-    issue(z0 - 1, ra);
-    issue(z0, rb);
-    finish(ra, P0);
-    issue(z0 + 1, ra);
-    finish(rb, P1);
-    issue(z0 + 2, rb);
-    finish(ra, P2);
+    {
+        Raw rc;
+        issue(z0 - 1, ra);
+        issue(z0, rb);
+        issue(z0 + 1, rc);
+        finish(z0 - 1, ra, P0);
+        finish(z0, rb, P1);
+        issue(z0 + 2, rb);
+        finish(z0 + 1, rc, P2);
+    }
     auto step = [&](int z, const Plane<R> &m, const Plane<R> &o, const Plane<R> &p, Plane<R> &slot,
                     const Raw &arrived, Raw &next) -> bool {
         issue(z + 3, next);
         emit(z, m, o, p);
         if (z + 1 >= z1) return false;
-        finish(arrived, slot);   // slot (held plane z-1) now holds plane z+2
+        finish(z + 2, arrived, slot);   // slot (held plane z-1) now holds plane z+2
         return true;
     };
     for (int z = z0;; z += 6) {
@@ -618,35 +701,64 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *stab, cons
     }
 }
 
-// Edge strips of kEdge output columns each (x = 0..29 and nx-29..nx) share one
-// wavefront when both x-PML strips fit inside them.
-constexpr int kEdge = 30;
-
-template <typename R>
-__host__ __device__ __forceinline__ bool split_edges(const LevelArgs<R> &L) {
-    return L.nx >= 2 * kEdge && L.lox >= 1 && L.lox <= kEdge && L.hix >= L.nx - kEdge;
-}
-
-template <typename R>
-int x_tiles(const LevelArgs<R> &L) {
-    return split_edges(L) ? 1 + ceil_div(L.nx - 2 * kEdge + 1, kTileX) : ceil_div(L.nx + 1, kTileX);
-}
-
-// Grid of one stencil launch.  PART 0 covers every tile.  With split edges the
-// tiles divide into an interior set (x tiles 1.. and y tiles whose four rows
-// all lie between the y-PML strips, PART 1), which needs no x/y stretching
-// and so compiles to fewer registers, and the remaining border set (PART 2).
-// The two parts are launched back to back; a fused norm spans both through
-// block_offset / total_blocks.
+// Tiles of one stencil launch: a wavefront covers a tile of columns, its rows and a chunk of tz
+// planes; a block holds four wavefronts that follow each other.
+//   Edge tiles hold both x-PML strips: `strip` output columns at each end of a row, strip + 2 lanes
+//   each, and as many rows as fill the wavefront (strip 30, 14 or 6: 1, 2 or 4 rows).  Every
+//   other tile is then free of x stretching (inner tiles of 62 columns from column `strip` on).
+//   Rows in the tensor form cost about twice those in the shell form, so the strip is the one with
+//   the least work a plane of rows (row_cost): on 89 columns with a 4-cell PML 14-column strips
+//   take 2 units a row where 30-column ones take 3 (4h level of a 352^3 grid: apply 9.6 -> 8.4 us, J2 11.4 -> 10.6 us).
+//   Without a strip that fits (no edge tiles) the columns are cut into tiles of 62 as they come.
+// Where the tiling allows, the inner tiles of rows between the y-PML strips may run as a launch of
+// their own (PART 1), which compiles to fewer registers, and the rest (PART 2) before it;
+// PART 0 covers everything.  A fused norm spans both launches through block_offset / total_blocks.
 struct TileMap {
-    int ntx, nty, tz;
-    int yt_lo, nyi;        // interior y tiles: yt_lo .. yt_lo + nyi - 1
+    int strip, rows;       // edge tiles: output columns at each end (0: none), rows a wavefront
+    int nxi;               // inner x tiles
+    int nyt;               // groups of four rows (one block of inner tiles; a multiple of `rows`)
+    int yt_lo, nyi;        // groups of four rows of the inner launch: yt_lo .. yt_lo + nyi - 1
+    int tz;
     int block_offset;      // index of this launch's first block among all blocks of the call
     int total_blocks;      // blocks over all launches of the call
 };
 
+// work a row: inner tiles count one, tiles in the tensor form two
+template <typename R>
+double row_cost(const LevelArgs<R> &L, int strip) {
+    if (strip == 0) {
+        int cost = 0;
+        for (int x0 = 0; x0 <= L.nx; x0 += kTileX)
+            cost += std::max(1, x0) >= L.lox && std::min(x0 + kTileX - 1, L.nx - 1) <= L.hix ? 1 : 2;
+        return cost;
+    }
+    return ceil_div(L.nx + 1 - 2 * strip, kTileX) + 2.0 * (2 * (strip + 2)) / 64;
+}
+
+template <typename R>
+TileMap make_tiles(const LevelArgs<R> &L, int tz) {
+    TileMap M = {};
+    M.tz = tz;
+    double best = row_cost(L, 0);
+    for (int strip : {30, 14, 6}) {
+        if (L.nx < 2 * strip || L.lox < 1 || L.lox > strip || L.hix < L.nx - strip) continue;
+        const double c = row_cost(L, strip);
+        if (c < best) best = c, M.strip = strip;
+    }
+    M.rows = M.strip ? 64 / (2 * (M.strip + 2)) : 1;
+    M.nxi = M.strip ? ceil_div(L.nx + 1 - 2 * M.strip, kTileX) : ceil_div(L.nx + 1, kTileX);
+    M.nyt = ceil_div(L.ny + 1, kWavesY * M.rows) * M.rows;
+    M.total_blocks = ((M.strip ? M.nyt / M.rows : 0) + M.nyt * M.nxi) * ceil_div(L.nz + 1, tz);
+    return M;
+}
+
+// Four wavefronts a SIMD (128 registers) for single precision: the shifted fused Jacobi would take
+// 136 and run with three (2h at 352^3: 36.1 -> 42.6 us)
+template <typename R>
+constexpr int kWavesPerSimd = sizeof(R) == sizeof(float) ? 4 : 1;
+
 template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, int PART>
-__global__ void __launch_bounds__(64 * kWavesY) k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g,
+__global__ void __launch_bounds__(64 * kWavesY, kWavesPerSimd<R>) k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g,
                                                  const TY *__restrict__ base, TY *__restrict__ y, R omegaJ, TileMap M,
                                                  RedBuf rb, KState *st, Scales sc, Batch bt) {
     // XCD-aware order of (tile, slot) pairs: block b runs on XCD b % 8; each XCD takes a
@@ -674,45 +786,58 @@ __global__ void __launch_bounds__(64 * kWavesY) k_stencil(LevelArgs<R> L, const 
         sc.y = slot_scale(sc.y, sl);
     }
     const R mul[4] = {load_mul<R, TX>(sc.x), load_mul<R, TG>(sc.g), load_mul<R, TY>(sc.b), store_mul<R, TY>(sc.y)};
-    extern __shared__ unsigned char smem_raw[];
-    R *stab = reinterpret_cast<R *>(smem_raw);   // alpha pieces, then (FP32) the shell quintics
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    R *etab = reinterpret_cast<R *>(smem_raw);   // alpha pieces, then (FP32) the shell quintics
+    R *ctab = etab + 20 * L.nk;
     const int tid = threadIdx.x + 64 * threadIdx.y;
     // the level's window of table intervals only (at 4h almost every node is in the clamped one)
-    for (int i = tid; i < L.nk * 20; i += 64 * kWavesY) stab[i] = L.atab[L.kb * 20 + i];
+    for (int i = tid; i < L.nk * 20; i += 64 * kWavesY) etab[i] = L.etab[L.kb * 20 + i];
     if (scaled_coordinate<R>())
-        for (int i = tid; i < L.nck * 24; i += 64 * kWavesY) stab[L.nk * 20 + i] = L.ctab[L.cb * 24 + i];
+        for (int i = tid; i < L.nck * 24; i += 64 * kWavesY) ctab[i] = L.ctab[L.cb * 24 + i];
     __syncthreads();
 
-    const int ntx = M.ntx, nty = M.nty;
+    // the wavefront's tile, rows and chunk: in scalar registers
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.y);
     int xt, yt, zc;
-    if (PART == 0) {
-        xt = t % ntx;
-        t /= ntx;
-        yt = t % nty;
-        zc = t / nty;
-    } else if (PART == 1) {
-        const int nxi = ntx - 1;
-        xt = 1 + t % nxi;
-        t /= nxi;
+    bool edge = false;
+    if (PART == 1) {
+        xt = t % M.nxi;
+        t /= M.nxi;
         yt = M.yt_lo + t % M.nyi;
         zc = t / M.nyi;
-    } else {
-        // per z chunk: the edge x tile of every y tile, then the inner x tiles of the y tiles outside the interior
-        const int per_z = nty + (nty - M.nyi) * (ntx - 1);
+    } else if (PART == 2) {
+        // per chunk of planes the edge blocks, then the inner tiles of the rows PART 1 leaves
+        const int neb = M.nyt / M.rows, per_z = neb + (M.nyt - M.nyi) * M.nxi;
         zc = t / per_z;
-        int u = t - zc * per_z;
-        if (u < nty) {
-            xt = 0;
-            yt = u;
-        } else {
-            u -= nty;
-            xt = 1 + u % (ntx - 1);
-            const int yo = u / (ntx - 1);
-            yt = yo < M.yt_lo ? yo : yo + M.nyi;
+        int v = t - zc * per_z;
+        edge = v < neb;
+        xt = 0;
+        yt = v;
+        if (!edge) {
+            v -= neb;
+            xt = v % M.nxi;
+            yt = v / M.nxi;
+            if (yt >= M.yt_lo) yt += M.nyi;
         }
+    } else {
+        // the blocks of neighbouring tiles follow each other, so that they run together and the cache
+        // merges the sectors that two of them write: per `rows` groups of rows one edge block, then
+        // their inner tiles, x fastest
+        const int ne = MODE != M_RESID_R && M.strip ? 1 : 0, unit = ne + M.rows * M.nxi;
+        const int q = t / unit, nu = M.nyt / M.rows;
+        int v = t - q * unit;
+        zc = q / nu;
+        edge = v < ne;
+        v -= ne;
+        xt = edge ? 0 : v % M.nxi;
+        yt = edge ? q - zc * nu : (q - zc * nu) * M.rows + v / M.nxi;
     }
     const int lane = threadIdx.x;
-    const int yg = yt * kWavesY + threadIdx.y;
+    const int yg = yt * kWavesY + wave;   // the row (edge tiles: the group of rows)
+    // rows yg - 1 .. yg + 1 inside the box and free of stretching
+    const bool y_inner = yg >= max(L.loy, 2) && yg <= min(L.hiy, L.ny - 2);
+    // planes za - 1 .. zb + 1 inside the box and planes za .. zb free of stretching
+    auto z_inner = [&](int za, int zb) { return za >= max(L.loz, 2) && zb <= min(L.hiz, L.nz - 2); };
     if (MODE == M_RESID_R) {
         // Fused residual + full weighting, first pass: x tiles of 60 fine columns
         // (lanes 0..63 hold x = 60 xt - 1 .. 60 xt + 62; the residual is valid on
@@ -727,63 +852,75 @@ __global__ void __launch_bounds__(64 * kWavesY) k_stencil(LevelArgs<R> L, const 
         double nrm = 0.0;
         if (yg <= L.ny) {
             const bool yi = (yg >= L.loy && yg <= L.hiy) || yg < 1 || yg > L.ny - 1;
-            if (xi && yi)
-                march<R, TX, TG, TY, MODE, SHIFT, false, true, true>(L, stab, x, g, base, y, omegaJ, mul, xg, yg, 2 * Z0 - 1,
-                                                                     2 * Z1, false, nrm, Z0);
+            const int za = 2 * Z0 - 1, zb = 2 * Z1;
+            // lanes 1..63 read columns 60 xt .. 60 xt + 62
+            const bool inner = xi && y_inner && z_inner(za, zb - 1) && xt >= 1 && 60 * xt + 62 <= L.nx - 1;
+#define HELM_MARCH_R(XI, YI, IN)                                                                                     \
+    march<R, TX, TG, TY, MODE, SHIFT, false, XI, YI, IN>(L, etab, ctab, x, g, base, y, omegaJ, mul, xg, yg, za, zb, \
+                                                         false, nrm, Z0)
+            if (inner)
+                HELM_MARCH_R(true, true, true);
+            else if (xi && yi)
+                HELM_MARCH_R(true, true, false);
             else if (xi)
-                march<R, TX, TG, TY, MODE, SHIFT, false, true, false>(L, stab, x, g, base, y, omegaJ, mul, xg, yg, 2 * Z0 - 1,
-                                                                      2 * Z1, false, nrm, Z0);
+                HELM_MARCH_R(true, false, false);
             else if (yi)
-                march<R, TX, TG, TY, MODE, SHIFT, false, false, true>(L, stab, x, g, base, y, omegaJ, mul, xg, yg, 2 * Z0 - 1,
-                                                                      2 * Z1, false, nrm, Z0);
+                HELM_MARCH_R(false, true, false);
             else
-                march<R, TX, TG, TY, MODE, SHIFT, false, false, false>(L, stab, x, g, base, y, omegaJ, mul, xg, yg,
-                                                                       2 * Z0 - 1, 2 * Z1, false, nrm, Z0);
+                HELM_MARCH_R(false, false, false);
+#undef HELM_MARCH_R
         }
         return;
     }
     const int z0 = zc * M.tz;
     const int z1 = min(z0 + M.tz, L.nz + 1);
-    // x tiling: with split edges, tile 0 holds both x edge strips (lanes 0..31:
-    // x = -1..30, lanes 32..63: x = nx-30..nx+1; lanes 31 and 32 are halo only),
-    // so every other tile is free of x stretching; otherwise 62-column tiles.
-    int xg;
-    bool out_lane, xi;
-    if (split_edges(L)) {
-        if (xt == 0) {
-            xg = lane < 32 ? lane - 1 : L.nx - kEdge + (lane - 32);
-            out_lane = (lane >= 1 && lane <= kEdge) || (lane >= 33 && lane <= 62);
-            xi = (L.lox <= 1 && L.hix >= L.nx - 1);
-        } else {
-            xg = kEdge - 1 + (xt - 1) * kTileX + lane;
-            out_lane = (lane >= 1 && lane <= kTileX && xg <= L.nx - kEdge);
-            xi = true;
-        }
-    } else {
-        xg = xt * kTileX - 1 + lane;
-        out_lane = (lane >= 1 && lane <= kTileX && xg <= L.nx);
-        const int xa = max(1, xt * kTileX), xb = min(xt * kTileX + kTileX - 1, L.nx - 1);
-        xi = (xa > xb) || (xa >= L.lox && xb <= L.hix);
-    }
     double nrm = 0.0;
-    if (PART == 1) {   // interior tiles: unit x/y weights on every row by construction
-        march<R, TX, TG, TY, MODE, SHIFT, NORM, true, true>(L, stab, x, g, base, y, omegaJ, mul, xg, yg, z0, z1, out_lane,
-                                                            nrm);
-    } else if (yg <= L.ny) {
-        const bool yi = (yg >= L.loy && yg <= L.hiy) || yg < 1 || yg > L.ny - 1;
-        if (xi && yi)
-            march<R, TX, TG, TY, MODE, SHIFT, NORM, true, true>(L, stab, x, g, base, y, omegaJ, mul, xg, yg, z0, z1,
-                                                                out_lane, nrm);
-        else if (xi)
-            march<R, TX, TG, TY, MODE, SHIFT, NORM, true, false>(L, stab, x, g, base, y, omegaJ, mul, xg, yg, z0, z1,
-                                                                 out_lane, nrm);
-        else if (yi)
-            march<R, TX, TG, TY, MODE, SHIFT, NORM, false, true>(L, stab, x, g, base, y, omegaJ, mul, xg, yg, z0, z1,
-                                                                 out_lane, nrm);
-        else
-            march<R, TX, TG, TY, MODE, SHIFT, NORM, false, false>(L, stab, x, g, base, y, omegaJ, mul, xg, yg, z0, z1,
-                                                                  out_lane, nrm);
+    int xg, yl = yg;                      // the lane's column and row
+    bool out, xi, yi, x_inner = false;    // x_inner: every column an output lane reads lies inside the box
+    bool rows_here = yg <= L.ny;
+    if (edge) {
+        // rows of 2 (strip + 2) lanes: x = -1 .. strip, then nx - strip .. nx + 1; the first and last lane
+        // of each strip only supply the halo
+        const int ls = M.strip + 2, sub = lane / (2 * ls), j = lane - sub * 2 * ls, half = j >= ls ? 1 : 0;
+        const int i = j - half * ls, ya = yg * M.rows;
+        yl = ya + sub;
+        xg = half ? L.nx - M.strip + i : i - 1;
+        out = i >= 1 && i <= M.strip && yl <= L.ny;
+        xi = false;
+        yi = ya >= L.loy && ya + M.rows - 1 <= L.hiy;
+        rows_here = ya <= L.ny;
+    } else {
+        if (M.strip) {
+            xg = M.strip - 1 + xt * kTileX + lane;
+            out = lane >= 1 && lane <= kTileX && xg <= L.nx - M.strip;
+            xi = x_inner = true;   // columns strip - 1 .. nx - strip + 1
+        } else {
+            xg = xt * kTileX - 1 + lane;
+            out = lane >= 1 && lane <= kTileX && xg <= L.nx;
+            const int xa = max(1, xt * kTileX), xb = min(xt * kTileX + kTileX - 1, L.nx - 1);
+            xi = (xa > xb) || (xa >= L.lox && xb <= L.hix);
+            x_inner = xi && xt >= 1 && xt * kTileX + kTileX <= L.nx - 1;
+        }
+        yi = (yg >= L.loy && yg <= L.hiy) || yg < 1 || yg > L.ny - 1;
     }
+#define HELM_MARCH(XI, YI, IN, YG)                                                                                   \
+    march<R, TX, TG, TY, MODE, SHIFT, NORM, XI, YI, IN>(L, etab, ctab, x, g, base, y, omegaJ, mul, xg, YG, z0, z1,  \
+                                                        out, nrm)
+    if (!rows_here)
+        ;
+    else if (x_inner && y_inner && z_inner(z0, z1 - 1))
+        HELM_MARCH(true, true, true, yg);
+    else if (xi && yi)
+        HELM_MARCH(true, true, false, yg);
+    else if (PART == 1)   // inner rows: no stretching
+        ;
+    else if (xi)
+        HELM_MARCH(true, false, false, yg);
+    else if (yi)
+        HELM_MARCH(false, true, false, yl);
+    else
+        HELM_MARCH(false, false, false, yl);
+#undef HELM_MARCH
     if (NORM) {
         block_reduce_store(nrm, rb.partials + M.block_offset + tile);
         norm_epilogue(rb, M.total_blocks, st);
@@ -1052,38 +1189,34 @@ hipError_t launch_stencil(const LevelArgs<R> &L, const StencilCall &c, const Red
     // the Jacobi modes read the stored D^-1 of the operator
     if ((c.mode == M_JSWEEP || c.mode == M_JAC2 || c.mode == M_JAC2_ADD) && !L.dinv[c.shifted ? 1 : 0])
         return hipErrorInvalidValue;
-    TileMap M;
+    const int fam = (c.mode == M_JAC2 || c.mode == M_JAC2_ADD) ? 1 : 0;
+    const int nyt = ceil_div(L.ny + 1, kWavesY);
+    const int tz = L.tz[fam] > 0 ? L.tz[fam] : pick_tz(ceil_div(L.nx + 1, kTileX), nyt, L.nz + 1);
     if (c.mode == M_RESID_R) {
         if (c.norm) return hipErrorInvalidValue;
-        M.ntx = std::max(1, ceil_div((L.nx >> 1) - 1, 30));
-        M.nty = ceil_div(L.ny + 1, kWavesY);
-        M.tz = std::max(1, (L.tz[0] > 0 ? L.tz[0] : pick_tz(M.ntx, M.nty, L.nz + 1)) / 2);   // coarse planes per chunk
-        M.yt_lo = M.nyi = 0;
-        M.block_offset = 0;
-        M.total_blocks = M.ntx * M.nty * ceil_div(L.nz >> 1, M.tz);
+        TileMap M = {};   // x tiles of 60 columns, no edge tiles
+        M.rows = 1;
+        M.nxi = std::max(1, ceil_div((L.nx >> 1) - 1, 30));
+        M.nyt = nyt;
+        M.tz = std::max(1, tz / 2);   // coarse planes per chunk
+        M.total_blocks = M.nxi * nyt * ceil_div(L.nz >> 1, M.tz);
         return launch_stencil_part<R, TX, TG, TY, 0>(L, c, rb, M, M.total_blocks, s);
     }
-    M.ntx = x_tiles(L);
-    M.nty = ceil_div(L.ny + 1, kWavesY);
-    const int fam = (c.mode == M_JAC2 || c.mode == M_JAC2_ADD) ? 1 : 0;
-    M.tz = L.tz[fam] > 0 ? L.tz[fam] : pick_tz(M.ntx, M.nty, L.nz + 1);
-    const int nzc = ceil_div(L.nz + 1, M.tz);
-    const int blocks = M.ntx * M.nty * nzc;
-    // interior y tiles: all kWavesY rows inside [loy, hiy]
-    M.yt_lo = ceil_div(L.loy, kWavesY);
-    M.nyi = std::max(0, (L.hiy + 1) / kWavesY - M.yt_lo);
-    M.block_offset = 0;
-    M.total_blocks = blocks;
-    if (L.split[fam] && split_edges(L) && M.ntx > 1 && M.nyi > 0) {
-        const int bi = (M.ntx - 1) * M.nyi * nzc;
-        const int bb = blocks - bi;
-        hipError_t e = launch_stencil_part<R, TX, TG, TY, 2>(L, c, rb, M, bb, s);
-        if (e != hipSuccess) return e;
-        M.block_offset = bb;
-        return launch_stencil_part<R, TX, TG, TY, 1>(L, c, rb, M, bi, s);
+    TileMap M = make_tiles(L, tz);
+    if (L.split[fam] && M.strip) {
+        // groups of four rows all inside [loy, hiy]
+        M.yt_lo = ceil_div(L.loy, kWavesY);
+        M.nyi = std::max(0, (L.hiy + 1) / kWavesY - M.yt_lo);
+        const int bi = M.nxi * M.nyi * ceil_div(L.nz + 1, tz), bb = M.total_blocks - bi;
+        if (bi > 0 && bb > 0) {
+            const hipError_t e = launch_stencil_part<R, TX, TG, TY, 2>(L, c, rb, M, bb, s);
+            if (e != hipSuccess) return e;
+            M.block_offset = bb;
+            return launch_stencil_part<R, TX, TG, TY, 1>(L, c, rb, M, bi, s);
+        }
+        M.yt_lo = M.nyi = 0;
     }
-    M.yt_lo = M.nyi = 0;
-    return launch_stencil_part<R, TX, TG, TY, 0>(L, c, rb, M, blocks, s);
+    return launch_stencil_part<R, TX, TG, TY, 0>(L, c, rb, M, M.total_blocks, s);
 }
 
 }  // namespace helm
