@@ -16,8 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libhelm.so")
 OBJ_DIR = os.path.join(HERE, "_build")
-SOURCES = ["stencil.hip", "stencil_fp64.hip", "stencil_mixed.hip", "transfer.hip", "vector.hip", "adjoint.hip",
-           "helm.hip", "noalloc.hip"]
+SOURCES = ["stencil.hip", "stencil_fp64.hip", "stencil_mixed.hip", "transfer.hip", "vector.hip",
+           "transpose.hip", "adjoint.hip", "helm.hip", "noalloc.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
