@@ -292,7 +292,7 @@ hipError_t launch_jac1(const LevelArgs<R> &L, int shifted, double omegaJ, const 
 template <typename R>
 hipError_t launch_dinv(const LevelArgs<R> &L, int shifted, R *out, hipStream_t s);   // out = D^-1 per node
 
-// Adjoint gradient (adjoint.hip): y = [g -] op^T x (op A, or B when shifted; g == nullptr:
+// Adjoint gradient (transpose.hip, adjoint.hip): y = [g -] op^T x (op A, or B when shifted; g == nullptr:
 // no residual), y = Q_h^T w (of conj(w) when conj_in), y_i = (d_i op x)_i in m = 1/c^2
 // (which 0: A, 1: Q_h), the per-node gradient terms accumulated into gacc, and their sum
 // onto the physical nodes.

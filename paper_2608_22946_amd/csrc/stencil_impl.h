@@ -191,6 +191,7 @@ struct RowCoef {
 
 // A table piece in LDS is read with 16-byte loads (ds_read_b128; the pieces are multiples of 16 B
 // from an aligned base): 24 floats of a node's quintics take 6 loads instead of 12.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 template <int N>
@@ -269,6 +270,16 @@ __device__ __forceinline__ void shell_coef(const LevelArgs<float> &L, const floa
     for (int m = 0; m < 4; ++m) C[m] = horner5(c + 6 * m, t);
 }
 __device__ __forceinline__ void shell_coef(const LevelArgs<double> &, const double *, float, double (&)[4]) {}
+// 1 / C_0: the row's D^-1 where it is free of stretching
+__device__ __forceinline__ float shell_dinv(const LevelArgs<float> &L, const float *ctab, float s) {
+    const float k = __builtin_amdgcn_fmed3f(truncf(s), (float)L.cb, (float)(L.cb + L.nck - 1));
+    const char *p = reinterpret_cast<const char *>(ctab) + piece_offset(k, (float)L.cb, 96.0f);
+    const f32x4 a = reinterpret_cast<const f32x4 *>(p)[0];
+    const f32x2 b = reinterpret_cast<const f32x2 *>(p)[2];
+    const float c[6] = {a.x, a.y, a.z, a.w, b.x, b.y};
+    return __builtin_amdgcn_rcpf(horner5(c, s - k));
+}
+__device__ __forceinline__ double shell_dinv(const LevelArgs<double> &, const double *, float) { return 0; }
 
 // per-node value a level's coefficient evaluation reads
 template <typename R>
@@ -464,7 +475,6 @@ __device__ void norm_epilogue(const RedBuf &rb, int nblocks, KState *st) {
 // offset in a scalar register and the lane's byte offset in the row in a vector register, so that
 // no address arithmetic runs on the vector unit.  Stores of lanes without an output are dropped
 // by the descriptor's bound (their offset is kNoStore) instead of by a branch.
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr unsigned kNoStore = 0xffffff00u;   // past every plane (at most 4097^2 nodes of 16 B)
@@ -505,6 +515,14 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t b, unsigned lan
 // plane base is wave-uniform (scalar registers).  INNER: every plane and row the wave reads
 // lies inside the box and every row it forms is free of stretching, so nothing is masked
 // and one coefficient form remains; most waves of a large level are of this kind.
+// The unshifted fused Jacobi of an FP32 level forms D^-1 = 1 / C_0 of the rows of its inner tiles from
+// the per-node values: 4 bytes a node of each row instead of 8 more (fine level at 352^3: 355 -> 331 us).
+// The shifted ones keep the stored D^-1: theirs is complex, and their levels fit in the cache.
+template <typename R>
+constexpr bool own_dinv(int mode, bool shifted) {
+    return scaled_coordinate<R>() && !shifted && mode == M_JAC2;
+}
+
 template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, bool XI, bool YI,
           bool INNER>
 __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, const R *ctab, const TX *__restrict__ x,
@@ -517,6 +535,7 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
     constexpr bool JAC = (MODE == M_JAC2 || MODE == M_JAC2_ADD);
     constexpr bool RESTRICT = (MODE == M_RESID_R);
     constexpr bool NEED_G = (MODE != M_APPLY);
+    constexpr bool OWN_D = INNER && own_dinv<R>(MODE, SHIFT);
     const bool x_int = (xg >= 1 && xg <= L.nx - 1);
     const int xc = min(max(xg, 0), L.nx);
     const int ym = max(yg - 1, 0), yc = min(yg, L.ny), yp = min(yg + 1, L.ny);
@@ -552,6 +571,7 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
         TX va, vb, vc;     // operand rows (not in the Jacobi modes)
         TG ga, gb, gc;     // right-hand side rows (Jacobi modes; gb alone in the others)
         DT da, db, dc;     // D^-1 rows (Jacobi modes; db alone in the sweep mode)
+        float ca, cp;      // per-node values of the other rows (where D^-1 is formed from them)
         TY bb;             // base at the centre (fused Jacobi + base)
         float cb;          // per-node coefficient value at the centre
     };
@@ -577,9 +597,14 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
             r.ga = row(g, rm);
             r.gb = row(g, r0);
             r.gc = row(g, rp);
-            r.da = row(dinv, rm);
-            r.db = row(dinv, r0);
-            r.dc = row(dinv, rp);
+            if constexpr (OWN_D) {
+                r.ca = row(vnode, rm);
+                r.cp = row(vnode, rp);
+            } else {
+                r.da = row(dinv, rm);
+                r.db = row(dinv, r0);
+                r.dc = row(dinv, rp);
+            }
             if constexpr (MODE == M_JAC2_ADD) r.bb = row(base, r0);
         }
         r.cb = row(vnode, r0);
@@ -592,6 +617,10 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
             b = dq<R>(r.vb, mx);
             c = dq<R>(r.vc, mx);
             if constexpr (NEED_G) P.gc = dq<R>(r.gb, mg);
+        } else if constexpr (OWN_D) {
+            a = zscale(shell_dinv(L, ctab, r.ca), dq<R>(r.ga, mg));
+            b = zscale(shell_dinv(L, ctab, r.cb), dq<R>(r.gb, mg));
+            c = zscale(shell_dinv(L, ctab, r.cp), dq<R>(r.gc, mg));
         } else {
             // fused two-sweep Jacobi: the operand is t = D^-1 g at every loaded node
             a = zmul(Z<R>{r.da.re, r.da.im}, dq<R>(r.ga, mg));
@@ -605,7 +634,7 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
             if (!(zok && rp_ok)) c = zero;
         }
         P.cc = r.cb;
-        if constexpr (JAC || SWEEP) P.dc = Z<R>{r.db.re, r.db.im};
+        if constexpr ((JAC && !OWN_D) || SWEEP) P.dc = Z<R>{r.db.re, r.db.im};
         if constexpr (MODE == M_JAC2_ADD) P.bc = dq<R>(r.bb, mb);
         plane_partials<R, XI, YI>(a, b, c, wx, wy, P);
     };
@@ -632,7 +661,11 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
             res = zadd(o.p0, zscale(omegaJ, zmul(o.dc, zsub(o.gc, Hv))));
         } else {
             // omega t + omega D^-1 (g - omega H t) with D^-1 g = t: neither g nor omega t is kept
-            const Z<R> dh = zmul(o.dc, Hv);
+            Z<R> dh;
+            if constexpr (OWN_D)
+                dh = zscale(shell_dinv(L, ctab, o.cc), Hv);
+            else
+                dh = zmul(o.dc, Hv);
             res = {omega2 * o.p0.r - omegasq * dh.r, omega2 * o.p0.i - omegasq * dh.i};
         }
         if constexpr (!INNER) {
@@ -752,15 +785,20 @@ TileMap make_tiles(const LevelArgs<R> &L, int tz) {
     return M;
 }
 
-// Four wavefronts a SIMD (128 registers) for single precision: the shifted fused Jacobi would take
-// 136 and run with three (2h at 352^3: 36.1 -> 42.6 us)
+// Wavefronts a SIMD in single precision: four (128 registers), and three (168) where four spill too
+// much: the fused Jacobi + base (V-cycle on the 2h level of a 352^3 grid: 312 -> 296 us), and the unshifted
+// fused Jacobi, which runs on the fine level (352^3: 331 -> 323 us).  The shifted one takes 136
+// and is better with four (2h at 352^3: 41 -> 37 us).
 template <typename R>
-constexpr int kWavesPerSimd = sizeof(R) == sizeof(float) ? 4 : 1;
+constexpr int waves_per_simd(int mode, bool shifted) {
+    if (sizeof(R) != sizeof(float)) return 1;
+    return mode == M_JAC2_ADD || (mode == M_JAC2 && !shifted) ? 3 : 4;
+}
 
 template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, int PART>
-__global__ void __launch_bounds__(64 * kWavesY, kWavesPerSimd<R>) k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g,
-                                                 const TY *__restrict__ base, TY *__restrict__ y, R omegaJ, TileMap M,
-                                                 RedBuf rb, KState *st, Scales sc, Batch bt) {
+__global__ void __launch_bounds__(64 * kWavesY, (waves_per_simd<R>(MODE, SHIFT)))
+k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, const TY *__restrict__ base,
+          TY *__restrict__ y, R omegaJ, TileMap M, RedBuf rb, KState *st, Scales sc, Batch bt) {
     // XCD-aware order of (tile, slot) pairs: block b runs on XCD b % 8; each XCD takes a
     // contiguous range of u = tile * slots + slot, so the slots of one tile run back to
     // back on one XCD and share the tile's per-node values and D^-1 through its L2.
@@ -834,10 +872,11 @@ __global__ void __launch_bounds__(64 * kWavesY, kWavesPerSimd<R>) k_stencil(Leve
     }
     const int lane = threadIdx.x;
     const int yg = yt * kWavesY + wave;   // the row (edge tiles: the group of rows)
-    // rows yg - 1 .. yg + 1 inside the box and free of stretching
-    const bool y_inner = yg >= max(L.loy, 2) && yg <= min(L.hiy, L.ny - 2);
-    // planes za - 1 .. zb + 1 inside the box and planes za .. zb free of stretching
-    auto z_inner = [&](int za, int zb) { return za >= max(L.loz, 2) && zb <= min(L.hiz, L.nz - 2); };
+    // rows yg - 1 .. yg + 1 inside the box and row yg free of stretching (hd = 1: all three)
+    constexpr int hd = own_dinv<R>(MODE, SHIFT) ? 1 : 0;
+    const bool y_inner = yg >= max(L.loy + hd, 2) && yg <= min(L.hiy - hd, L.ny - 2);
+    // planes za - 1 .. zb + 1 inside the box and planes za .. zb free of stretching (hd = 1: all)
+    auto z_inner = [&](int za, int zb) { return za >= max(L.loz + hd, 2) && zb <= min(L.hiz - hd, L.nz - 2); };
     if (MODE == M_RESID_R) {
         // Fused residual + full weighting, first pass: x tiles of 60 fine columns
         // (lanes 0..63 hold x = 60 xt - 1 .. 60 xt + 62; the residual is valid on
@@ -893,13 +932,14 @@ __global__ void __launch_bounds__(64 * kWavesY, kWavesPerSimd<R>) k_stencil(Leve
         if (M.strip) {
             xg = M.strip - 1 + xt * kTileX + lane;
             out = lane >= 1 && lane <= kTileX && xg <= L.nx - M.strip;
-            xi = x_inner = true;   // columns strip - 1 .. nx - strip + 1
+            xi = true;             // columns strip - 1 .. nx - strip + 1
+            x_inner = !hd || (L.lox <= M.strip - 1 && L.hix >= L.nx - M.strip + 1);
         } else {
             xg = xt * kTileX - 1 + lane;
             out = lane >= 1 && lane <= kTileX && xg <= L.nx;
             const int xa = max(1, xt * kTileX), xb = min(xt * kTileX + kTileX - 1, L.nx - 1);
             xi = (xa > xb) || (xa >= L.lox && xb <= L.hix);
-            x_inner = xi && xt >= 1 && xt * kTileX + kTileX <= L.nx - 1;
+            x_inner = xi && xt * kTileX - 1 >= max(1, hd * L.lox) && xt * kTileX + kTileX <= min(L.nx - 1, hd ? L.hix : L.nx);
         }
         yi = (yg >= L.loy && yg <= L.hiy) || yg < 1 || yg > L.ny - 1;
     }
