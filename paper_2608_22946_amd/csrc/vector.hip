@@ -162,14 +162,17 @@ __device__ bool reduce_partials(const D2 (&acc)[NS], const RedBuf &rb, D2 *out) 
 
 // In the last block: total of every slot over all blocks, in a fixed order.
 // Thread t owns slot q = t % (2 NS) and the blocks b = t / (2 NS) + k * G
-// (G = blockDim / (2 NS) groups); its loads are independent and unrolled, then
-// the G group sums are added in order.
+// (G = blockDim / (2 NS) groups); its loads are independent and unrolled.  The group sums
+// are then added by eight threads a slot and those eight by one (one thread a slot added up to
+// 512 of them in a chain, most of them of groups without a block).
 template <int NS>
 __device__ void sum_partials(const RedBuf &rb, D2 *out) {
     if (gridDim.x == 1) return;   // reduce_partials has written the totals
     constexpr int NQ = 2 * NS;
     constexpr int G = kRedThreads / NQ > 0 ? kRedThreads / NQ : 1;
-    __shared__ double grp[kRedThreads];
+    constexpr int H = 8;
+    static_assert(2 * kSlots * H <= kRedThreads, "eight threads a slot");
+    __shared__ double grp[kRedThreads], sub[H * NQ];
     const int nb = gridDim.x;
     const int t = threadIdx.x;
     double v = 0.0;
@@ -180,9 +183,17 @@ __device__ void sum_partials(const RedBuf &rb, D2 *out) {
     }
     grp[t] = v;
     __syncthreads();
+    if (t < H * NQ) {
+        const int used = G < nb ? G : nb;
+        double s = 0.0;
+        for (int g = t / NQ; g < used; g += H) s += grp[g * NQ + t % NQ];
+        sub[t] = s;
+    }
+    __syncthreads();
     if (t < NQ) {
         double s = 0.0;
-        for (int g = 0; g < G; ++g) s += grp[g * NQ + t];
+#pragma unroll
+        for (int h = 0; h < H; ++h) s += sub[h * NQ + t];
         if (t & 1)
             out[t >> 1].i = s;
         else
@@ -855,10 +866,15 @@ __global__ void __launch_bounds__(256) k_velocity_check(const float *__restrict_
     }
 }
 
-// blocks of a reduction: at least ~4 elements per thread, so that small (cache
-// resident) vectors spend their time on loads rather than on block reductions
+// Blocks of a reduction.  Up to 2048 elements: one, which needs no pass over partials.  Then one element
+// a thread up to 64 blocks, because every step of the grid-stride loop waits for its loads (eleven
+// sums over 36k elements with four steps in 9 blocks 13.8 us, with one step in 35 blocks 9.5; the
+// five-vector Gram kernel on 5k elements 10.2 -> 8.4, on 16k 11.2 -> 8.7 us).  More blocks only
+// for four elements a thread: the last block's pass grows with them (three vectors of 262k
+// elements: 8.3 us in 66 blocks, 9.2 in 256).
 int red_blocks(long long n) {
-    long long b = (n + 4 * kRedThreads - 1) / (4 * kRedThreads);
+    const long long one = (n + kRedThreads - 1) / kRedThreads, four = (n + 4 * kRedThreads - 1) / (4 * kRedThreads);
+    long long b = n <= 2 * kRedThreads ? 1 : std::max(std::min(one, 64ll), four);
     if (b < 1) b = 1;
     if (b > kRedMaxBlocks) b = kRedMaxBlocks;
     return (int)b;

@@ -10,15 +10,16 @@ from workloads import grf_velocity
 
 pytestmark = pytest.mark.gpu
 
-# a reduction block holds 1024 threads and takes up to 4096 elements
-SIZES = [1, 63, 65, 1023, 1024, 1025, 4095, 4096, 4097, 8193, 300001]
+# a reduction block holds 1024 threads; one block up to 2048 elements, then one element a thread in up
+# to 64 blocks, then four elements a thread in up to 256
+SIZES = [1, 63, 65, 1023, 1024, 1025, 2048, 2049, 4097, 8193, 65535, 65537, 262145, 300001]
 
 
 @pytest.mark.parametrize("dtype", [np.complex64, np.complex128])
 def test_dots_of_every_count_and_size(dtype):
     """Against numpy in extended precision.  The sums are FP64 with at most
-    ceil(n / (256 * 1024)) + 5 + 10 + 4 + 16 + 34 + 34 additions in a chain (thread, wavefront,
-    waves, blocks): under 128 units of 2^-53 of sum |v| |w|."""
+    4 + 6 + 16 + 26 + 64 + 8 additions in a chain (thread, wavefront, waves, a group's blocks,
+    groups): under 128 units of 2^-53 of sum |v| |w|."""
     from paper_2608_22946_amd import helm
     rng = np.random.default_rng(5)
     for i, n in enumerate(SIZES):
