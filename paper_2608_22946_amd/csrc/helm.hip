@@ -492,8 +492,14 @@ struct Eng {
     // sum_j y_j J(P_j) minimises ||q - sum_j y_j P_{j+1}|| (normal equations of the
     // FP64 Gram matrix, Cholesky).
     hipError_t bottom(const T *q, T *e) {
+        T *Zb[kM4Max];
+        HIP_CHK(bottom_basis(q, Zb));
+        return launch_combine<T, T>(e, nullptr, (const T *const *)Zb, H->opt.m_4h, nn(2), Ln->st_bottom, false, s);
+    }
+    // its basis J(P_j) in Zb and coefficients y in the bottom state
+    hipError_t bottom_basis(const T *q, T **Zb) {
         const int m = H->opt.m_4h;
-        T *P[kM4Max + 1], *Zb[kM4Max];
+        T *P[kM4Max + 1];
         P[0] = const_cast<T *>(q);
         for (int j = 1; j <= m; ++j) P[j] = v(Ln->P4[j]);
         for (int j = 0; j < m; ++j) Zb[j] = v(Ln->Z4[j]);
@@ -501,19 +507,18 @@ struct Eng {
             HIP_CHK(jacobi(2, true, H->opt.nJ_4h, H->opt.omega_4h, P[j], Zb[j]));
             HIP_CHK(stencil(2, M_APPLY, true, 0.0, Zb[j], nullptr, nullptr, P[j + 1]));
         }
-        HIP_CHK(launch_gram<T>((const T *const *)P, m + 1, nn(2), Ln->st_bottom, Ln->rb, s));
-        HIP_CHK((launch_combine<T, T>(e, nullptr, (const T *const *)Zb, m, nn(2), Ln->st_bottom, false, s)));
-        return hipSuccess;
+        return launch_gram<T>((const T *const *)P, m + 1, nn(2), Ln->st_bottom, Ln->rb, s);
     }
 
     // V^sigma_2h(q), eq. shifted-auxiliary-cycle
     hipError_t vcycle(const T *q, T *out) {
         const helm_options &o = H->opt;
-        T *y = v(Ln->vy), *r = v(Ln->vr), *q4 = v(Ln->P4[0]), *e4 = v(Ln->e4);
+        T *y = v(Ln->vy), *r = v(Ln->vr), *q4 = v(Ln->P4[0]), *Zb[kM4Max];
         HIP_CHK(jacobi(1, true, o.nJ_2h, o.omega_2h, q, y));                 // y = J(B_2h, q)
         HIP_CHK(resid_restrict(1, true, y, q, q4));                          // q_4h = R(q - B y)
-        HIP_CHK(bottom(q4, e4));                                             // e_4h = C_4h(q_4h)
-        HIP_CHK(launch_prolong_add<T>(H->geom[2], H->geom[1], e4, y, s));   // y~ = y + P e_4h
+        HIP_CHK(bottom_basis(q4, Zb));                                       // e_4h = C_4h(q_4h) = sum_j y_j Zb_j
+        HIP_CHK(launch_prolong_combined<T>(H->geom[2], H->geom[1], (const T *const *)Zb, o.m_4h, Ln->st_bottom, y,
+                                           s));                              // y~ = y + P e_4h
         HIP_CHK(stencil(1, M_RESID, true, 0.0, y, q, nullptr, r));           // q - B y~
         if (o.nJ_2h == 2) {
             HIP_CHK(stencil(1, M_JAC2_ADD, true, o.omega_2h, nullptr, r, y, out));   // y~ + J(B, q - B y~)

@@ -252,6 +252,10 @@ hipError_t launch_restrict_y(const Geom &fine, const Geom &coarse, const T *w, T
 template <typename T, typename TF = T>
 hipError_t launch_prolong_add(const Geom &coarse, const Geom &fine, const T *c, TF *f, hipStream_t s,
                               Scale sc = {1.0f, nullptr}, Scale sf = {1.0f, nullptr});
+// f += P sum_j y_j Z_j, j < nz <= kM4Max (y of the state)
+template <typename T>
+hipError_t launch_prolong_combined(const Geom &coarse, const Geom &fine, const T *const *Z, int nz, const KState *st, T *f,
+                                   hipStream_t s);
 
 template <typename T>
 hipError_t launch_dots(const T *const *V, int nv, const T *w, bool norm, long long n, int epi, KState *st, int k,

@@ -80,22 +80,61 @@ __global__ void __launch_bounds__(256) k_restrict_y(Geom F, Geom C, const T *__r
 // and X + 1 with weight 1/2 each; coarse boundary nodes contribute zero and
 // fine boundary nodes are left unchanged.  Each coarse value is loaded once per
 // cell instead of once per fine node, and the two x-neighbouring fine nodes of
-// a cell are adjacent in memory.
-template <typename T, typename TF>
-__global__ void __launch_bounds__(256) k_prolong_add(Geom C, Geom F, const T *__restrict__ c, TF *__restrict__ f,
-                                                    Scale sc, Scale sf, Batch bt) {
+// a cell are adjacent in memory.  Every value is loaded before the first store (a row's loads could
+// not pass the stores of the row before: four memory latencies in a chain), and a cell's two
+// nodes of a row go out together.
+//
+// NV > 0: the coarse vector is sum_j y_j Z_j, the bottom solver's combination (y of the state st),
+// formed here instead of by a launch of its own.  Bound by latency on small levels (V-cycle of a 132^3
+// grid 101 -> 95 us for both changes) and by memory on large ones, where neither changes the time.
+template <typename T, int NV>
+struct CoarseVecs {
+    const T *v[NV > 0 ? NV : 1];
+};
+template <typename T, typename TF, int NV>
+__global__ void __launch_bounds__(256) k_prolong_add(Geom C, Geom F, CoarseVecs<T, NV> cv, TF *__restrict__ f,
+                                                    const KState *st, Scale sc, Scale sf, Batch bt) {
     using R = std::conditional_t<is_half<TF>(), float, real_of<TF>>;   // FP16-stored vectors add in FP32
+    constexpr int N = NV > 0 ? NV : 1;
     const int sl = blockIdx.z / C.n[2];   // batched slots follow each other along z
     if (slot_off(bt, sl)) return;
     const int X = blockIdx.x * blockDim.x + threadIdx.x, Y = blockIdx.y * blockDim.y + threadIdx.y, Z = blockIdx.z % C.n[2];
     if (X >= C.n[0] || Y >= C.n[1]) return;
-    c = slot_ptr(c, C.nn, sl);
+#pragma unroll
+    for (int j = 0; j < N; ++j) cv.v[j] = slot_ptr(cv.v[j], C.nn, sl);
     f = slot_ptr(f, F.nn, sl);
+    st = slot_ptr(st, 1, sl);
     sc = slot_scale(sc, sl);
     sf = slot_scale(sf, sl);
+    // the fine nodes 2X, 2X + 1 of rows 2Y + j, planes 2Z + k: at most F.n - 1
+    struct Two {
+        TF a, b;
+    } o[2][2];
+    TF *const corner = f + (long long)(2 * Z) * F.sy + (long long)(2 * Y) * F.sx + 2 * X;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) __builtin_memcpy(&o[k][j], corner + k * F.sy + j * F.sx, sizeof(Two));
+    // coarse corner values
+    T cval[2][2][2][N];
+#pragma unroll
+    for (int cz = 0; cz < 2; ++cz)
+#pragma unroll
+        for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+            for (int cx = 0; cx < 2; ++cx)
+#pragma unroll
+                for (int j = 0; j < N; ++j)
+                    cval[cz][cy][cx][j] = cv.v[j][(long long)(Z + cz) * C.sy + (long long)(Y + cy) * C.sx + X + cx];
     // c16 operands: coarse values to true units, fine values through the fine scale
     const R mc = load_mul<R, T>(sc), mfl = load_mul<R, TF>(sf), mfs = store_mul<R, TF>(sf);
-    // coarse corner values, zero outside the coarse interior
+    R yr[N], yi[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        yr[j] = NV > 0 ? (R)st->y[j][0] : (R)1;
+        yi[j] = NV > 0 ? (R)st->y[j][1] : (R)0;
+    }
+    // zero outside the coarse interior
     R cr[2][2][2], ci[2][2][2];
 #pragma unroll
     for (int cz = 0; cz < 2; ++cz)
@@ -106,22 +145,22 @@ __global__ void __launch_bounds__(256) k_prolong_add(Geom C, Geom F, const T *__
                 const int Xc = X + cx, Yc = Y + cy, Zc = Z + cz;
                 const bool in = Xc >= 1 && Xc <= C.n[0] - 1 && Yc >= 1 && Yc <= C.n[1] - 1 && Zc >= 1 &&
                                 Zc <= C.n[2] - 1;
-                T v;
-                v.re = 0;
-                v.im = 0;
-                if (in) v = c[(long long)Zc * C.sy + (long long)Yc * C.sx + Xc];
-                cr[cz][cy][cx] = (R)v.re * mc;
-                ci[cz][cy][cx] = (R)v.im * mc;
+                R vr = 0, vi = 0;
+#pragma unroll
+                for (int j = 0; j < N; ++j) {
+                    const R zr = (R)cval[cz][cy][cx][j].re, zi = (R)cval[cz][cy][cx][j].im;
+                    vr = NV > 0 ? vr + (yr[j] * zr - yi[j] * zi) : zr;
+                    vi = NV > 0 ? vi + (yr[j] * zi + yi[j] * zr) : zi;
+                }
+                cr[cz][cy][cx] = in ? vr * mc : (R)0;
+                ci[cz][cy][cx] = in ? vi * mc : (R)0;
             }
     const R half = (R)0.5;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        const int z = 2 * Z + k;
-        if (z < 1) continue;   // z <= 2 (nc - 1) + 1 = F.n[2] - 1 always
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const int y = 2 * Y + j;
-            if (y < 1) continue;
+            if (2 * Z + k < 1 || 2 * Y + j < 1) continue;   // boundary rows
             // the four coarse values of this fine row, weighted along z and y
             R pr[2], pi[2];
 #pragma unroll
@@ -135,13 +174,11 @@ __global__ void __launch_bounds__(256) k_prolong_add(Geom C, Geom F, const T *__
                 pr[cx] = j ? half * (zr[0] + zr[1]) : zr[0];
                 pi[cx] = j ? half * (zi[0] + zi[1]) : zi[0];
             }
-            TF *row = f + (long long)z * F.sy + (long long)y * F.sx + 2 * X;
-            if (X >= 1) {   // fine node 2X (x = 0 is a boundary node)
-                const TF o = row[0];
-                row[0] = to_stored<TF, R>((R)o.re * mfl + pr[0], (R)o.im * mfl + pi[0], mfs);
-            }
-            const TF o = row[1];   // fine node 2X + 1
-            row[1] = to_stored<TF, R>((R)o.re * mfl + half * (pr[0] + pr[1]), (R)o.im * mfl + half * (pi[0] + pi[1]), mfs);
+            Two v = o[k][j];
+            if (X >= 1)   // fine node 2X (x = 0 is a boundary node: it keeps its value)
+                v.a = to_stored<TF, R>((R)v.a.re * mfl + pr[0], (R)v.a.im * mfl + pi[0], mfs);
+            v.b = to_stored<TF, R>((R)v.b.re * mfl + half * (pr[0] + pr[1]), (R)v.b.im * mfl + half * (pi[0] + pi[1]), mfs);
+            __builtin_memcpy(corner + k * F.sy + j * F.sx, &v, sizeof(Two));
         }
     }
 }
@@ -188,11 +225,40 @@ hipError_t launch_prolong_add(const Geom &coarse, const Geom &fine, const T *c, 
     if ((is_half<T>() && !sc.qs) || (is_half<TF>() && !sf.qs)) return hipErrorInvalidValue;
     const Batch &bt = cur_batch();
     const int bx = cell_block_x(coarse);
-    hipLaunchKernelGGL((k_prolong_add<T, TF>), cell_grid(coarse, bx, bt.n), dim3(bx, 256 / bx), 0, s, coarse, fine, c, f,
-                       sc, sf, bt);
+    hipLaunchKernelGGL((k_prolong_add<T, TF, 0>), cell_grid(coarse, bx, bt.n), dim3(bx, 256 / bx), 0, s, coarse, fine,
+                       CoarseVecs<T, 0>{{c}}, f, nullptr, sc, sf, bt);
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_prolong_combined(const Geom &coarse, const Geom &fine, const T *const *Z, int nz, const KState *st, T *f,
+                                   hipStream_t s) {
+    if (fine.n[0] != 2 * coarse.n[0] || fine.n[1] != 2 * coarse.n[1] || fine.n[2] != 2 * coarse.n[2])
+        return hipErrorInvalidValue;
+    const Batch &bt = cur_batch();
+    const int bx = cell_block_x(coarse);
+    const Scale one = {1.0f, nullptr};
+#define HELM_PC(NV)                                                                                                   \
+    case NV: {                                                                                                        \
+        CoarseVecs<T, NV> cv;                                                                                         \
+        for (int j = 0; j < NV; ++j) cv.v[j] = Z[j];                                                                  \
+        hipLaunchKernelGGL((k_prolong_add<T, T, NV>), cell_grid(coarse, bx, bt.n), dim3(bx, 256 / bx), 0, s, coarse,  \
+                           fine, cv, f, st, one, one, bt);                                                            \
+        break;                                                                                                        \
+    }
+    switch (nz) {
+        HELM_PC(1) HELM_PC(2) HELM_PC(3) HELM_PC(4) HELM_PC(5) HELM_PC(6) HELM_PC(7) HELM_PC(8)
+    default:
+        return hipErrorInvalidValue;
+    }
+#undef HELM_PC
+    return hipGetLastError();
+}
+
+template hipError_t launch_prolong_combined<c32>(const Geom &, const Geom &, const c32 *const *, int, const KState *,
+                                                 c32 *, hipStream_t);
+template hipError_t launch_prolong_combined<c64>(const Geom &, const Geom &, const c64 *const *, int, const KState *,
+                                                 c64 *, hipStream_t);
 template hipError_t launch_restrict<c32>(const Geom &, const Geom &, const c32 *, c32 *, hipStream_t);
 template hipError_t launch_restrict<c64>(const Geom &, const Geom &, const c64 *, c64 *, hipStream_t);
 template hipError_t launch_restrict_y<c32, c32>(const Geom &, const Geom &, const c32 *, c32 *, hipStream_t, Scale);

@@ -59,3 +59,14 @@ def test_coarse_solve_cycle_lengths(m_2h):
     r = p.rand(1, 232)
     err = rel(to_np(p.g.coarse_solve(p.dev(r))), p.o.k2h(r.astype(complex)))
     assert err <= 1e-8, err
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("m_4h", [1, 2, 3, 5, 8])
+def test_vcycle_basis_lengths(m_4h, precision):
+    """V^sigma_2h, whose prolongation forms the bottom solver's combination itself, for each number of
+    basis vectors; the bars are those of the bottom solver."""
+    p = Pair(grf_velocity(20, 12, 16, seed=25, corr_len=4.0), 4, precision, m_4h=m_4h)
+    q = p.rand(1, 233)
+    err = rel(to_np(p.g.vcycle(p.dev(q))), p.o.vcycle(q.astype(complex)))
+    assert err <= p.tol(1e-9 if m_4h <= 5 else FP32_MAP_GATE, FP32_MAP_GATE if m_4h <= 5 else 1e-2), err
