@@ -25,7 +25,7 @@
 // the operand is the FP32 velocity.
 //
 // What bounds it.  On a large level the memory path of the march: halving the vector instructions
-// of its interior rows (124 -> 56 per plane) left the apply at 352^3 where it was (244 -> 245 us),
+// of its interior rows (124 -> 56 per plane) left the apply at 352^3 where it was (242 -> 246 us),
 // one, two or three planes in flight measure the same, and without its stores the same loads
 // take 108 us (67 us with one row load instead of three) of the 231 us that they take with
 // them; a linear stream of the same arrays takes 140 us.  On a coarse level, which the cache
@@ -795,6 +795,15 @@ constexpr int waves_per_simd(int mode, bool shifted) {
     return mode == M_JAC2_ADD || (mode == M_JAC2 && !shifted) ? 3 : 4;
 }
 
+// Whether a kernel has the INNER variant.  The unshifted FP32 apply and residuals run on the fine level,
+// where the memory path bounds them and waves of two speeds cost more than the shorter code gives
+// (352^3, with and without it: apply 246 and 239 us, residual 308 and 299, restricted 295 and 288;
+// the unshifted 2h apply takes 29 us either way).
+template <typename R>
+constexpr bool has_inner(int mode, bool shifted) {
+    return sizeof(R) != sizeof(float) || shifted || !(mode == M_APPLY || mode == M_RESID || mode == M_RESID_R);
+}
+
 template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, int PART>
 __global__ void __launch_bounds__(64 * kWavesY, (waves_per_simd<R>(MODE, SHIFT)))
 k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, const TY *__restrict__ base,
@@ -893,7 +902,7 @@ k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, co
             const bool yi = (yg >= L.loy && yg <= L.hiy) || yg < 1 || yg > L.ny - 1;
             const int za = 2 * Z0 - 1, zb = 2 * Z1;
             // lanes 1..63 read columns 60 xt .. 60 xt + 62
-            const bool inner = xi && y_inner && z_inner(za, zb - 1) && xt >= 1 && 60 * xt + 62 <= L.nx - 1;
+            const bool inner = has_inner<R>(MODE, SHIFT) && xi && y_inner && z_inner(za, zb - 1) && xt >= 1 && 60 * xt + 62 <= L.nx - 1;
 #define HELM_MARCH_R(XI, YI, IN)                                                                                     \
     march<R, TX, TG, TY, MODE, SHIFT, false, XI, YI, IN>(L, etab, ctab, x, g, base, y, omegaJ, mul, xg, yg, za, zb, \
                                                          false, nrm, Z0)
@@ -948,7 +957,7 @@ k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, co
                                                         out, nrm)
     if (!rows_here)
         ;
-    else if (x_inner && y_inner && z_inner(z0, z1 - 1))
+    else if (has_inner<R>(MODE, SHIFT) && x_inner && y_inner && z_inner(z0, z1 - 1))
         HELM_MARCH(true, true, true, yg);
     else if (xi && yi)
         HELM_MARCH(true, true, false, yg);
