@@ -214,7 +214,7 @@ size_t carve(helm_hierarchy *H, char *base, const int N[3], const helm_options &
             np = std::max(np, (size_t)stencil_blocks(g[l].n[0], g[l].n[1], g[l].n[2], kTzMin));
         Ln.rb.partials = c.take<double>(np * B);
         Ln.nslot = B;
-        Ln.pstride = (long long)np;
+        Ln.pstride = Ln.rb.cap = (long long)np;
         Ln.rb.counter = c.take<unsigned>(64);
         // small results: 256 doubles, or 2 kRedSlots per slot for the batched norms of the outer solve
         Ln.dscratch = c.take<double>(kScratchDoubles);

@@ -9,6 +9,7 @@
 #include <string>
 
 #include "helm.h"
+#include "tiles.h"
 
 namespace helm {
 
@@ -16,8 +17,6 @@ constexpr int kMMax = 12;       // longest Krylov restart supported (m_h, m_2h, 
 constexpr int kM4Max = 8;       // longest bottom (s-step) basis
 constexpr int kSstepMax = 2;    // longest fine-level smoothing cycle computed with an s-step basis
 constexpr int kKMax = 128;      // most table intervals
-constexpr int kTileX = 62;      // output nodes per wavefront along x (64 lanes, 1-node halo each side)
-constexpr int kWavesY = 4;      // wavefronts (rows y) per workgroup
 constexpr int kRedBlocks = 1024;
 constexpr int kRedStride = kMMax + 2;   // partial-sum slots per block (dots + norm)
 constexpr int kRedMaxBlocks = 256;      // most blocks of a vector reduction (red_blocks)
@@ -160,6 +159,7 @@ struct KState {
 struct RedBuf {
     double *partials;    // [kRedBlocks][kRedStride][2]
     unsigned *counter;   // zero between kernels
+    long long cap;       // doubles at `partials`, per batched slot
 };
 
 // Right-hand sides batched in one launch (helm_options.batch).  Slot s = blockIdx.y
@@ -319,7 +319,6 @@ hipError_t launch_grad_to_velocity(const float *grad_m, const float *vel, const 
 hipError_t launch_grad_phys(const double *gacc, const Geom &fine, int n_pml, const int nphys[3], float *out,
                             hipStream_t s);
 
-int stencil_blocks(int nx, int ny, int nz, int tz);   // grid size of launch_stencil on a level (tz 0: default)
 // z planes per stencil wavefront: any depth kTzMin..kTzMax may be fixed; setup times the candidates
 constexpr int kTzMin = 2, kTzMax = 64;
 constexpr int kTzCandidates[] = {2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 20, 24, 32, 40, 48, 64};
@@ -334,7 +333,6 @@ hipError_t launch_scaled_eta(const float *c, long long n, double factor, float *
 
 hipError_t launch_velocity_check(const float *v, long long n, const RedBuf &rb, double *out, hipStream_t s);
 
-inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 
 // record the message helm_last_error(NULL) returns on this thread; returns st
 helm_status thread_error(helm_status st, const char *msg);

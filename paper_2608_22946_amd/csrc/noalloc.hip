@@ -48,6 +48,7 @@ hipError_t run(void *base, int k, const void *const *V, const void *w, long long
     helm::RedBuf rb;
     rb.partials = static_cast<double *>(base);
     rb.counter = reinterpret_cast<unsigned *>(static_cast<char *>(base) + kCounterOffset);
+    rb.cap = kPartialBytes / sizeof(double);
     // the ticket must start at zero: cleared by a fill kernel (no memset node under capture)
     hipError_t e = helm::launch_fill_zero<helm::c32>(reinterpret_cast<helm::c32 *>(rb.counter), 256 / sizeof(helm::c32), s);
     if (e != hipSuccess) return e;

@@ -4,14 +4,6 @@
 
 namespace helm {
 
-// upper bound over every tiling: the plain x tiles and a wavefront of edge strips a row
-int stencil_blocks(int nx, int ny, int nz, int tz) {
-    const int ntx = 2 + ceil_div(nx + 1, kTileX);
-    const int nty = ceil_div(ny + 1, kWavesY);
-    if (tz <= 0) tz = pick_tz(ntx, nty, nz + 1);
-    return ntx * nty * ceil_div(nz + 1, tz);
-}
-
 template <typename R, typename TI, typename TO>
 hipError_t launch_qapply(const LevelArgs<R> &L, const TI *x, TO *y, hipStream_t s) {
     const int ntx = ceil_div(L.nx + 1, kQX), nty = ceil_div(L.ny + 1, 4), nzc = ceil_div(L.nz + 1, kQZ);

@@ -734,57 +734,6 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
     }
 }
 
-// Tiles of one stencil launch: a wavefront covers a tile of columns, its rows and a chunk of tz
-// planes; a block holds four wavefronts that follow each other.
-//   Edge tiles hold both x-PML strips: `strip` output columns at each end of a row, strip + 2 lanes
-//   each, and as many rows as fill the wavefront (strip 30, 14 or 6: 1, 2 or 4 rows).  Every
-//   other tile is then free of x stretching (inner tiles of 62 columns from column `strip` on).
-//   Rows in the tensor form cost about twice those in the shell form, so the strip is the one with
-//   the least work a plane of rows (row_cost): on 89 columns with a 4-cell PML 14-column strips
-//   take 2 units a row where 30-column ones take 3 (4h level of a 352^3 grid: apply 9.6 -> 8.4 us, J2 11.4 -> 10.6 us).
-//   Without a strip that fits (no edge tiles) the columns are cut into tiles of 62 as they come.
-// Where the tiling allows, the inner tiles of rows between the y-PML strips may run as a launch of
-// their own (PART 1), which compiles to fewer registers, and the rest (PART 2) before it;
-// PART 0 covers everything.  A fused norm spans both launches through block_offset / total_blocks.
-struct TileMap {
-    int strip, rows;       // edge tiles: output columns at each end (0: none), rows a wavefront
-    int nxi;               // inner x tiles
-    int nyt;               // groups of four rows (one block of inner tiles; a multiple of `rows`)
-    int yt_lo, nyi;        // groups of four rows of the inner launch: yt_lo .. yt_lo + nyi - 1
-    int tz;
-    int block_offset;      // index of this launch's first block among all blocks of the call
-    int total_blocks;      // blocks over all launches of the call
-};
-
-// work a row: inner tiles count one, tiles in the tensor form two
-template <typename R>
-double row_cost(const LevelArgs<R> &L, int strip) {
-    if (strip == 0) {
-        int cost = 0;
-        for (int x0 = 0; x0 <= L.nx; x0 += kTileX)
-            cost += std::max(1, x0) >= L.lox && std::min(x0 + kTileX - 1, L.nx - 1) <= L.hix ? 1 : 2;
-        return cost;
-    }
-    return ceil_div(L.nx + 1 - 2 * strip, kTileX) + 2.0 * (2 * (strip + 2)) / 64;
-}
-
-template <typename R>
-TileMap make_tiles(const LevelArgs<R> &L, int tz) {
-    TileMap M = {};
-    M.tz = tz;
-    double best = row_cost(L, 0);
-    for (int strip : {30, 14, 6}) {
-        if (L.nx < 2 * strip || L.lox < 1 || L.lox > strip || L.hix < L.nx - strip) continue;
-        const double c = row_cost(L, strip);
-        if (c < best) best = c, M.strip = strip;
-    }
-    M.rows = M.strip ? 64 / (2 * (M.strip + 2)) : 1;
-    M.nxi = M.strip ? ceil_div(L.nx + 1 - 2 * M.strip, kTileX) : ceil_div(L.nx + 1, kTileX);
-    M.nyt = ceil_div(L.ny + 1, kWavesY * M.rows) * M.rows;
-    M.total_blocks = ((M.strip ? M.nyt / M.rows : 0) + M.nyt * M.nxi) * ceil_div(L.nz + 1, tz);
-    return M;
-}
-
 // Wavefronts a SIMD in single precision: four (128 registers), and three (168) where four spill too
 // much: the fused Jacobi + base (V-cycle on the 2h level of a 352^3 grid: 312 -> 296 us), and the unshifted
 // fused Jacobi, which runs on the fine level (352^3: 331 -> 323 us).  The shifted one takes 136
@@ -1251,7 +1200,8 @@ hipError_t launch_stencil(const LevelArgs<R> &L, const StencilCall &c, const Red
         M.total_blocks = M.nxi * nyt * ceil_div(L.nz >> 1, M.tz);
         return launch_stencil_part<R, TX, TG, TY, 0>(L, c, rb, M, M.total_blocks, s);
     }
-    TileMap M = make_tiles(L, tz);
+    TileMap M = make_tiles(L.nx, L.ny, L.nz, L.lox, L.hix, tz);
+    if (c.norm && M.total_blocks > rb.cap) return hipErrorInvalidValue;   // a partial a block
     if (L.split[fam] && M.strip) {
         // groups of four rows all inside [loy, hiy]
         M.yt_lo = ceil_div(L.loy, kWavesY);

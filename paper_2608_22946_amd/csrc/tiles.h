@@ -1,0 +1,82 @@
+// Tiles of the stencil launches and the bound on their number.  Host code without HIP: the launches
+// and the size of the fused norm's partials come from the same counts.
+#pragma once
+
+#include <algorithm>
+
+namespace helm {
+
+constexpr int kTileX = 62;      // output nodes per wavefront along x (64 lanes, 1-node halo each side)
+constexpr int kWavesY = 4;      // wavefronts (rows y) per workgroup
+
+inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
+
+// Tiles of one stencil launch: a wavefront covers a tile of columns, its rows and a chunk of tz
+// planes; a block holds four wavefronts that follow each other.
+//   Edge tiles hold both x-PML strips: `strip` output columns at each end of a row, strip + 2 lanes
+//   each, and as many rows as fill the wavefront (strip 30, 14 or 6: 1, 2 or 4 rows).  Every
+//   other tile is then free of x stretching (inner tiles of 62 columns from column `strip` on).
+//   Rows in the tensor form cost about twice those in the shell form, so the strip is the one with
+//   the least work a plane of rows (row_cost): on 89 columns with a 4-cell PML 14-column strips
+//   take 2 units a row where 30-column ones take 3 (4h level of a 352^3 grid: apply 9.6 -> 8.4 us, J2 11.4 -> 10.6 us).
+//   Without a strip that fits (no edge tiles) the columns are cut into tiles of 62 as they come.
+// Where the tiling allows, the inner tiles of rows between the y-PML strips may run as a launch of
+// their own (PART 1), which compiles to fewer registers, and the rest (PART 2) before it;
+// PART 0 covers everything.  A fused norm spans both launches through block_offset / total_blocks.
+struct TileMap {
+    int strip, rows;       // edge tiles: output columns at each end (0: none), rows a wavefront
+    int nxi;               // inner x tiles
+    int nyt;               // groups of four rows (one block of inner tiles; a multiple of `rows`)
+    int yt_lo, nyi;        // groups of four rows of the inner launch: yt_lo .. yt_lo + nyi - 1
+    int tz;
+    int block_offset;      // index of this launch's first block among all blocks of the call
+    int total_blocks;      // blocks over all launches of the call
+};
+
+constexpr int kStrips[] = {30, 14, 6};
+
+// tiles of an nx x ny x nz level with the given strips (0: none)
+inline TileMap tile_counts(int nx, int ny, int nz, int strip, int tz) {
+    TileMap M = {};
+    M.tz = tz;
+    M.strip = strip;
+    M.rows = strip ? 64 / (2 * (strip + 2)) : 1;
+    M.nxi = ceil_div(nx + 1 - 2 * strip, kTileX);
+    M.nyt = ceil_div(ny + 1, kWavesY * M.rows) * M.rows;
+    M.total_blocks = ((strip ? M.nyt / M.rows : 0) + M.nyt * M.nxi) * ceil_div(nz + 1, tz);
+    return M;
+}
+
+// work a row: inner tiles count one, tiles in the tensor form two; columns lox .. hix are free of stretching
+inline double row_cost(int nx, int lox, int hix, int strip) {
+    if (strip == 0) {
+        int cost = 0;
+        for (int x0 = 0; x0 <= nx; x0 += kTileX)
+            cost += std::max(1, x0) >= lox && std::min(x0 + kTileX - 1, nx - 1) <= hix ? 1 : 2;
+        return cost;
+    }
+    return ceil_div(nx + 1 - 2 * strip, kTileX) + 2.0 * (2 * (strip + 2)) / 64;
+}
+
+inline TileMap make_tiles(int nx, int ny, int nz, int lox, int hix, int tz) {
+    int best_strip = 0;
+    double best = row_cost(nx, lox, hix, 0);
+    for (int strip : kStrips) {
+        if (nx < 2 * strip || lox < 1 || lox > strip || hix < nx - strip) continue;
+        const double c = row_cost(nx, lox, hix, strip);
+        if (c < best) best = c, best_strip = strip;
+    }
+    return tile_counts(nx, ny, nz, best_strip, tz);
+}
+
+// Upper bound of make_tiles' total_blocks over every width of the PML and every depth from tz on: the
+// number of partials a fused norm may write.  Taken over the tilings themselves, because the groups
+// of rows of a strip are rounded up to whole wavefronts (few rows: up to four times as many).
+inline int stencil_blocks(int nx, int ny, int nz, int tz) {
+    int most = tile_counts(nx, ny, nz, 0, tz).total_blocks;
+    for (int strip : kStrips)
+        if (nx >= 2 * strip) most = std::max(most, tile_counts(nx, ny, nz, strip, tz).total_blocks);
+    return most;
+}
+
+}  // namespace helm
