@@ -28,8 +28,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 N_PHYS, N_PML, H, TOL, SEED = 320, 16, 10.0, 1e-6, 2
 COUNTER_FILE = os.path.join(ROOT, "profiles", "stencil_apply_352_fp32_counters.txt")
-# the stencil kernels (template code) and the file that instantiates the FP32 / FP64 ones
-STENCIL_SRCS = [os.path.join(ROOT, "paper_2608_22946_amd", "csrc", f) for f in ("stencil_impl.h", "stencil.hip")]
+# the stencil kernels (template code), their tiling and the file that instantiates the FP32 ones
+STENCIL_SRCS = [os.path.join(ROOT, "paper_2608_22946_amd", "csrc", f)
+                for f in ("stencil_impl.h", "tiles.h", "stencil.hip")]
 
 
 def workload():
