@@ -508,13 +508,6 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t b, unsigned lan
     }
 }
 
-// One wavefront: rows y-1, y, y+1 at 64 consecutive x, marching planes z0..z1-1.
-// Every load reads an in-bounds node (indices clamped to the grid) and
-// boundary / out-of-box values are masked to zero afterwards, so the loads
-// carry no branches; the per-lane byte offsets inside a plane are fixed and the
-// plane base is wave-uniform (scalar registers).  INNER: every plane and row the wave reads
-// lies inside the box and every row it forms is free of stretching, so nothing is masked
-// and one coefficient form remains; most waves of a large level are of this kind.
 // The unshifted fused Jacobi of an FP32 level forms D^-1 = 1 / C_0 of the rows of its inner tiles from
 // the per-node values: 4 bytes a node of each row instead of 8 more (fine level at 352^3: 355 -> 331 us).
 // The shifted ones keep the stored D^-1: theirs is complex, and their levels fit in the cache.
@@ -523,6 +516,13 @@ constexpr bool own_dinv(int mode, bool shifted) {
     return scaled_coordinate<R>() && !shifted && mode == M_JAC2;
 }
 
+// One wavefront: rows y-1, y, y+1 at 64 consecutive x, marching planes z0..z1-1.
+// Every load reads an in-bounds node (indices clamped to the grid) and
+// boundary / out-of-box values are masked to zero afterwards, so the loads
+// carry no branches; the per-lane byte offsets inside a plane are fixed and the
+// plane base is wave-uniform (scalar registers).  INNER: every plane and row the wave reads
+// lies inside the box and every row it forms is free of stretching, so nothing is masked
+// and one coefficient form remains; most waves of a large level are of this kind.
 template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, bool XI, bool YI,
           bool INNER>
 __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, const R *ctab, const TX *__restrict__ x,
@@ -538,11 +538,11 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
     constexpr bool OWN_D = INNER && own_dinv<R>(MODE, SHIFT);
     const bool x_int = (xg >= 1 && xg <= L.nx - 1);
     const int xc = min(max(xg, 0), L.nx);
-    const int ym = max(yg - 1, 0), yc = min(yg, L.ny), yp = min(yg + 1, L.ny);
+    const MarchRows rows = march_rows(yg, L.ny);
     // node offsets: of the lane in a row (vector), of the three rows in a plane (scalar where the
     // wavefront has one row)
-    const unsigned lx = (unsigned)xc, r0 = (unsigned)(yc * (int)L.sx), rm = (unsigned)(ym * (int)L.sx),
-                   rp = (unsigned)(yp * (int)L.sx);
+    const unsigned lx = (unsigned)xc, r0 = (unsigned)(rows.c * (int)L.sx), rm = (unsigned)(rows.m * (int)L.sx),
+                   rp = (unsigned)(rows.p * (int)L.sx);
     auto load_row = [&](const auto *p, unsigned ro) {
         using E = std::remove_const_t<std::remove_reference_t<decltype(*p)>>;
         if constexpr (XI)
@@ -560,7 +560,7 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
         wx[0] = {w[0], w[1]}; wx[1] = {w[2], w[3]}; wx[2] = {w[4], w[5]};
     }
     if constexpr (!YI) {
-        const R *v = L.wy + 6 * yc;
+        const R *v = L.wy + 6 * rows.c;
         wy[0] = {v[0], v[1]}; wy[1] = {v[2], v[3]}; wy[2] = {v[4], v[5]};
     }
     const Z<R> zero = {0, 0};
@@ -651,7 +651,7 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
     // output plane z from planes m, o, p
     auto emit = [&](int z, const Plane<R> &m, const Plane<R> &o, const Plane<R> &p) {
         const bool zint = INNER || (z >= L.loz && z <= L.hiz);
-        const Z<R> Hv = row_value<R, XI && YI, SHIFT, INNER>(L, etab, ctab, m, o, p, zint, L.wz + 6 * z);
+        const Z<R> Hv = row_value<R, XI && YI, SHIFT, INNER>(L, etab, ctab, m, o, p, zint, L.wz + 6 * clamp_node(z, L.nz));
         Z<R> res;
         if constexpr (MODE == M_APPLY) {
             res = Hv;

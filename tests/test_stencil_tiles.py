@@ -48,12 +48,45 @@ int main() {
 
 
 def test_partials_hold_every_tiling(tmp_path):
+    _run(tmp_path, PROGRAM)
+
+
+# every row and plane that a march of any tiling forms: the rows and weight nodes it reads with exist
+ROWS_PROGRAM = r"""
+#include <cstdio>
+#include "tiles.h"
+using namespace helm;
+int main() {
+    for (int strip : {0, 30, 14, 6})
+        for (int ny = 2; ny <= 200; ++ny) {
+            const TileMap M = tile_counts(200, ny, ny, strip, 4);
+            for (int y = 0; y < M.nyt * kWavesY; y += M.rows) {   // a wavefront's rows y .. y + rows - 1
+                if (y > ny) continue;
+                for (int r = 0; r < M.rows; ++r) {
+                    const MarchRows m = march_rows(y + r, ny);
+                    for (int a : {m.m, m.c, m.p})
+                        if (a < 0 || a > ny) return std::printf("strip %d ny %d row %d: reads row %d\n", strip, ny, y + r, a);
+                }
+            }
+            for (int z = -1; z <= ny; ++z)   // the fused restriction starts at plane -1
+                if (clamp_node(z, ny) < 0 || clamp_node(z, ny) > ny) return std::printf("plane %d of %d\n", z, ny);
+        }
+    return 0;
+}
+"""
+
+
+def _run(tmp_path, program):
     src, exe = tmp_path / "tiles.cpp", tmp_path / "tiles"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2608_22946_amd", "csrc"),
                            str(src), "-o", str(exe)])
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+def test_marches_read_inside_the_grid(tmp_path):
+    _run(tmp_path, ROWS_PROGRAM)
 
 
 @pytest.mark.gpu
