@@ -651,7 +651,14 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
     // output plane z from planes m, o, p
     auto emit = [&](int z, const Plane<R> &m, const Plane<R> &o, const Plane<R> &p) {
         const bool zint = INNER || (z >= L.loz && z <= L.hiz);
-        const Z<R> Hv = row_value<R, XI && YI, SHIFT, INNER>(L, etab, ctab, m, o, p, zint, L.wz + 6 * clamp_node(z, L.nz));
+        // A row of the boundary is not formed but masked below.  Besides the work that this saves on thin
+        // levels, the branch keeps the compiler from drawing one plane's table reads into the next: without
+        // it the residual, the sweep and the fused restriction spill 20 to 55 registers at four wavefronts
+        // a SIMD, and the fused Jacobi takes 136.  With and without it, z depth 8: fused Jacobi at 352^3 366
+        // and 398 us, three sweeps 897 and 974, restriction at 208^3 74 and 88, residual at 208^3 70 and 75.
+        const bool interior = INNER || (r0_ok && z >= 1 && z <= L.nz - 1);
+        Z<R> Hv = zero;
+        if (interior) Hv = row_value<R, XI && YI, SHIFT, INNER>(L, etab, ctab, m, o, p, zint, L.wz + 6 * z);
         Z<R> res;
         if constexpr (MODE == M_APPLY) {
             res = Hv;
@@ -669,6 +676,7 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
             res = {omega2 * o.p0.r - omegasq * dh.r, omega2 * o.p0.i - omegasq * dh.i};
         }
         if constexpr (!INNER) {
+            // the condition again: kept over the row, `interior` spills five registers of the restriction
             if (!(r0_ok && z >= 1 && z <= L.nz - 1)) res = zero;
         }
         if constexpr (RESTRICT) {
@@ -734,14 +742,10 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
     }
 }
 
-// Wavefronts a SIMD in single precision: four (128 registers), and three (168) where four spill too
-// much: the fused Jacobi + base (V-cycle on the 2h level of a 352^3 grid: 312 -> 296 us), and the unshifted
-// fused Jacobi, which runs on the fine level (352^3: 331 -> 323 us).  The shifted one takes 136
-// and is better with four (2h at 352^3: 41 -> 37 us).
+// Wavefronts a SIMD: four in single precision (128 registers; no kernel spills), two of up to 256 in double.
 template <typename R>
-constexpr int waves_per_simd(int mode, bool shifted) {
-    if (sizeof(R) != sizeof(float)) return 1;
-    return mode == M_JAC2_ADD || (mode == M_JAC2 && !shifted) ? 3 : 4;
+constexpr int waves_per_simd() {
+    return sizeof(R) == sizeof(float) ? 4 : 1;
 }
 
 // Whether a kernel has the INNER variant.  The unshifted FP32 apply and residuals run on the fine level,
@@ -754,7 +758,7 @@ constexpr bool has_inner(int mode, bool shifted) {
 }
 
 template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, int PART>
-__global__ void __launch_bounds__(64 * kWavesY, (waves_per_simd<R>(MODE, SHIFT)))
+__global__ void __launch_bounds__(64 * kWavesY, waves_per_simd<R>())
 k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, const TY *__restrict__ base,
           TY *__restrict__ y, R omegaJ, TileMap M, RedBuf rb, KState *st, Scales sc, Batch bt) {
     // XCD-aware order of (tile, slot) pairs: block b runs on XCD b % 8; each XCD takes a

@@ -80,8 +80,8 @@ inline int stencil_blocks(int nx, int ny, int nz, int tz) {
 }
 
 // Rows and weight nodes that a wavefront reads.  A march goes past the grid on purpose (the last edge
-// tile's rows lie up to three beyond ny, the fused restriction starts at plane -1): what it forms
-// there is masked, and every index that it reads with is clamped to 0 .. n.
+// tile's rows lie up to three beyond ny, the fused restriction starts at plane -1): the indices that
+// it loads with are clamped to 0 .. n, and a row is formed with its weights inside the boundary only.
 constexpr int clamp_node(int a, int n) { return a < 0 ? 0 : (a > n ? n : a); }
 struct MarchRows {
     int m, c, p;   // rows y - 1, y, y + 1

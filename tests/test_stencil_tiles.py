@@ -68,8 +68,6 @@ int main() {
                         if (a < 0 || a > ny) return std::printf("strip %d ny %d row %d: reads row %d\n", strip, ny, y + r, a);
                 }
             }
-            for (int z = -1; z <= ny; ++z)   // the fused restriction starts at plane -1
-                if (clamp_node(z, ny) < 0 || clamp_node(z, ny) > ny) return std::printf("plane %d of %d\n", z, ny);
         }
     return 0;
 }
