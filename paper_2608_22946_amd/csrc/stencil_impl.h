@@ -807,14 +807,14 @@ k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, co
         zc = t / M.nyi;
     } else if (PART == 2) {
         // per chunk of planes the edge blocks, then the inner tiles of the rows PART 1 leaves
-        const int neb = M.nyt / M.rows, per_z = neb + (M.nyt - M.nyi) * M.nxi;
+        const int per_z = M.neb + (M.nyt - M.nyi) * M.nxi;
         zc = t / per_z;
         int v = t - zc * per_z;
-        edge = v < neb;
+        edge = v < M.neb;
         xt = 0;
         yt = v;
         if (!edge) {
-            v -= neb;
+            v -= M.neb;
             xt = v % M.nxi;
             yt = v / M.nxi;
             if (yt >= M.yt_lo) yt += M.nyi;
@@ -824,13 +824,15 @@ k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, co
         // merges the sectors that two of them write: per `rows` groups of rows one edge block, then
         // their inner tiles, x fastest
         const int ne = MODE != M_RESID_R && M.strip ? 1 : 0, unit = ne + M.rows * M.nxi;
-        const int q = t / unit, nu = M.nyt / M.rows;
-        int v = t - q * unit;
-        zc = q / nu;
+        const int per_z = M.neb + M.nyt * M.nxi;   // the last unit of a chunk may be shorter
+        zc = t / per_z;
+        int v = t - zc * per_z;
+        const int q = v / unit;
+        v -= q * unit;
         edge = v < ne;
         v -= ne;
         xt = edge ? 0 : v % M.nxi;
-        yt = edge ? q - zc * nu : (q - zc * nu) * M.rows + v / M.nxi;
+        yt = edge ? q : q * M.rows + v / M.nxi;
     }
     const int lane = threadIdx.x;
     const int yg = yt * kWavesY + wave;   // the row (edge tiles: the group of rows)

@@ -20,13 +20,17 @@ inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 //   the least work a plane of rows (row_cost): on 89 columns with a 4-cell PML 14-column strips
 //   take 2 units a row where 30-column ones take 3 (4h level of a 352^3 grid: apply 9.6 -> 8.4 us, J2 11.4 -> 10.6 us).
 //   Without a strip that fits (no edge tiles) the columns are cut into tiles of 62 as they come.
+//   The last edge block may have rows for fewer than `rows` groups; the groups without rows get no inner
+//   blocks (launched and left at once, they put a second block on some compute units of a thin
+//   level: A_h on 400 x 24 x 36 cells in FP64 at depth 8 took 12.1 us with them and takes 9.7, J2 13.9 and 10.6).
 // Where the tiling allows, the inner tiles of rows between the y-PML strips may run as a launch of
 // their own (PART 1), which compiles to fewer registers, and the rest (PART 2) before it;
 // PART 0 covers everything.  A fused norm spans both launches through block_offset / total_blocks.
 struct TileMap {
     int strip, rows;       // edge tiles: output columns at each end (0: none), rows a wavefront
     int nxi;               // inner x tiles
-    int nyt;               // groups of four rows (one block of inner tiles; a multiple of `rows`)
+    int nyt;               // groups of four rows (a block of inner tiles each)
+    int neb;               // blocks of edge tiles a chunk of planes (`rows` groups each)
     int yt_lo, nyi;        // groups of four rows of the inner launch: yt_lo .. yt_lo + nyi - 1
     int tz;
     int block_offset;      // index of this launch's first block among all blocks of the call
@@ -42,8 +46,9 @@ inline TileMap tile_counts(int nx, int ny, int nz, int strip, int tz) {
     M.strip = strip;
     M.rows = strip ? 64 / (2 * (strip + 2)) : 1;
     M.nxi = ceil_div(nx + 1 - 2 * strip, kTileX);
-    M.nyt = ceil_div(ny + 1, kWavesY * M.rows) * M.rows;
-    M.total_blocks = ((strip ? M.nyt / M.rows : 0) + M.nyt * M.nxi) * ceil_div(nz + 1, tz);
+    M.nyt = ceil_div(ny + 1, kWavesY);
+    M.neb = strip ? ceil_div(M.nyt, M.rows) : 0;
+    M.total_blocks = (M.neb + M.nyt * M.nxi) * ceil_div(nz + 1, tz);
     return M;
 }
 
@@ -70,8 +75,7 @@ inline TileMap make_tiles(int nx, int ny, int nz, int lox, int hix, int tz) {
 }
 
 // Upper bound of make_tiles' total_blocks over every width of the PML and every depth from tz on: the
-// number of partials a fused norm may write.  Taken over the tilings themselves, because the groups
-// of rows of a strip are rounded up to whole wavefronts (few rows: up to four times as many).
+// number of partials a fused norm may write.  Taken over the tilings themselves.
 inline int stencil_blocks(int nx, int ny, int nz, int tz) {
     int most = tile_counts(nx, ny, nz, 0, tz).total_blocks;
     for (int strip : kStrips)

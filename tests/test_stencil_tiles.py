@@ -60,7 +60,8 @@ int main() {
     for (int strip : {0, 30, 14, 6})
         for (int ny = 2; ny <= 200; ++ny) {
             const TileMap M = tile_counts(200, ny, ny, strip, 4);
-            for (int y = 0; y < M.nyt * kWavesY; y += M.rows) {   // a wavefront's rows y .. y + rows - 1
+            // a wavefront's rows y .. y + rows - 1 (edge tiles), y (inner tiles)
+            for (int y = 0; y < (strip ? M.neb * M.rows : M.nyt) * kWavesY; y += M.rows) {
                 if (y > ny) continue;
                 for (int r = 0; r < M.rows; ++r) {
                     const MarchRows m = march_rows(y + r, ny);
@@ -89,16 +90,16 @@ def test_marches_read_inside_the_grid(tmp_path):
 
 @pytest.mark.gpu
 def test_norm_of_more_blocks_than_the_least_partials():
-    """340 x 16 x 3932 cells at two planes a wavefront: 98350 blocks, where the partials' least size is 98304.
+    """620 x 16 x 3932 cells at two planes a wavefront: 102284 blocks, where the partials' least size is 98304.
     The norm that one preconditioner call reports is that of the residual of its result (both norms are of
     FP64 residuals that differ by rounding)."""
     import torch
     from paper_2608_22946_amd import helm
-    vel = torch.full((3929, 13, 337), 2000.0)
+    vel = torch.full((3929, 13, 617), 2000.0)
     H = helm.Hierarchy(vel, 10.0, 2 * 3.141592653589793 * 2000.0 / 60.0, 2, precision="fp64", tile_tz=2,
                        tile_split=0, max_outer=1)
     f = H.zeros(0)
-    f[1900, 8, 170] = 1e-3
+    f[1900, 8, 300] = 1e-3
     u, v, its, relres, rc = H.solve_checkpoint(f, 1e-12)
     assert (its, rc) == (1, helm.HELM_NOT_CONVERGED)
     b = H.apply(0, helm.OP_Q, f)
