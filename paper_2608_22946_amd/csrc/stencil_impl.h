@@ -491,21 +491,30 @@ __device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t b, unsigned lane_of
     else
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(b, lane_off, row_off, 0));
 }
+// A store at `off` + `row_off` of the buffer.  A 16-byte store takes its offset from the vector register alone
+// (split_row): with the row's part in a scalar register the compiler puts no wait state before the next
+// vector write to the data registers, which a store of more than 8 bytes reads late (the fused norm's
+// squares, formed in the same registers, reached memory in place of the imaginary part).  Two 8-byte stores
+// instead, each with half of every 16 bytes, cost the FP64 kernels 6 to 12% (352^3, depth 40: apply 466
+// and 415 us, residual 563 and 531, J2 631 and 589).
 template <typename T>
-__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t b, unsigned lane_off, unsigned row_off, T v) {
+constexpr bool split_row() { return sizeof(T) <= 8; }
+template <typename T>
+__device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t b, unsigned off, unsigned row_off, T v) {
     if constexpr (sizeof(T) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, lane_off, row_off, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, off, row_off, 0);
     else if constexpr (sizeof(T) == 8)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, lane_off, row_off, 0);
-    else {
-        // 16 bytes go out as two stores: a store of more than 8 bytes reads its data registers
-        // late, and with the row offset in a scalar register the compiler puts no wait state
-        // before the next vector write to them.  The fused norm's squares, formed in the same
-        // registers, then reached memory in place of the imaginary part.
-        const u32x4 w = __builtin_bit_cast(u32x4, v);
-        __builtin_amdgcn_raw_buffer_store_b64(u32x2{w.x, w.y}, b, lane_off, row_off, 0);
-        __builtin_amdgcn_raw_buffer_store_b64(u32x2{w.z, w.w}, b, lane_off + 8u, row_off, 0);
-    }
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, off, row_off, 0);
+    else
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, off, 0, 0);   // row_off: 0
+}
+// lane and row offsets of the stores of a row (nodes lx of the lane, r0 of the row); lanes without an output: kNoStore
+template <typename T>
+__device__ __forceinline__ void row_store_offsets(bool out, bool scalar_row, unsigned lx, unsigned r0, unsigned &off,
+                                                  unsigned &row_off) {
+    const bool split = split_row<T>() && scalar_row;
+    off = out ? (split ? lx : r0 + lx) * (unsigned)sizeof(T) : kNoStore;
+    row_off = split ? r0 * (unsigned)sizeof(T) : 0u;
 }
 
 // The unshifted fused Jacobi of an FP32 level forms D^-1 = 1 / C_0 of the rows of its inner tiles from
@@ -646,7 +655,8 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
     const int lane = threadIdx.x;
     const bool rstore = RESTRICT && (lane & 1) && lane >= 3 && lane <= 61 && yint && (xg >> 1) >= 1 && (xg >> 1) <= nxc - 1;
     Z<R> rcur = zero;
-    const unsigned store_off = out_lane ? (XI ? lx : r0 + lx) * (unsigned)sizeof(TY) : kNoStore;
+    unsigned store_off, store_row;
+    row_store_offsets<TY>(out_lane, XI, lx, r0, store_off, store_row);
     const R omega2 = (R)2 * omegaJ, omegasq = omegaJ * omegaJ;
     // output plane z from planes m, o, p
     auto emit = [&](int z, const Plane<R> &m, const Plane<R> &o, const Plane<R> &p) {
@@ -701,8 +711,7 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
                 res.r += o.bc.r;
                 res.i += o.bc.i;
             }
-            buf_store(plane_buf(y + (unsigned long long)(unsigned)z * sy, sy), store_off,
-                      XI ? r0 * (unsigned)sizeof(TY) : 0u, qz<TY>(res, my));
+            buf_store(plane_buf(y + (unsigned long long)(unsigned)z * sy, sy), store_off, store_row, qz<TY>(res, my));
             if constexpr (NORM) {
                 if (out_lane) nrm += (double)res.r * (double)res.r + (double)res.i * (double)res.i;
             }

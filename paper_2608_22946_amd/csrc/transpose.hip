@@ -119,7 +119,8 @@ __device__ __forceinline__ void march_t(const LevelArgs<R> &L, const R *etab, co
             r.g = buf_load<TG>(plane_buf(g + pg, sy), lx * (unsigned)sizeof(TG), r0 * (unsigned)sizeof(TG));
         }
     };
-    const unsigned store_off = out_lane ? lx * (unsigned)sizeof(TY) : kNoStore;
+    unsigned store_off, store_row;
+    row_store_offsets<TY>(out_lane, true, lx, r0, store_off, store_row);
     Z<R> acc0 = {0, 0}, acc1 = {0, 0}, acc2 = {0, 0};   // sums of the outputs in planes p - 1, p, p + 1
     const int here = wave * 64 + lane;
     // the first and last row have no outputs
@@ -191,7 +192,7 @@ __device__ __forceinline__ void march_t(const LevelArgs<R> &L, const R *etab, co
             Z<R> v = acc0;
             if constexpr (RESID) v = {(R)r.g.re - v.r, (R)r.g.im - v.i};
             if (!(inxy && z >= 1 && z <= L.nz - 1)) v = {0, 0};
-            buf_store(plane_buf(y + (unsigned long long)(unsigned)z * sy, sy), store_off, r0 * (unsigned)sizeof(TY),
+            buf_store(plane_buf(y + (unsigned long long)(unsigned)z * sy, sy), store_off, store_row,
                       TY{(decltype(TY{}.re))v.r, (decltype(TY{}.re))v.i});
         }
         acc0 = acc1;
