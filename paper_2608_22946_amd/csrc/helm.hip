@@ -1094,6 +1094,8 @@ std::mutex g_tile_mutex;
 std::map<TileKey, std::pair<int, int>> g_tile_cache;
 
 hipError_t tune_tiles(helm_hierarchy *H) {
+    for (int l = 0; l < 3; ++l)   // half the depth in coarse planes, or chosen at the launch
+        H->Lf[l].tz_restrict = H->Ld[l].tz_restrict = H->opt.tile_tz != 0 ? std::max(1, H->opt.tile_tz / 2) : 0;
     if (H->opt.tile_tz != 0 && H->opt.tile_split >= 0) {
         for (int l = 0; l < 3; ++l)
             for (int f = 0; f < 2; ++f) {

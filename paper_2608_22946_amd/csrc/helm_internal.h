@@ -115,6 +115,7 @@ struct LevelArgs {
     R sigma;
     // stencil tiling per kernel family ([0] apply / residual / sweep, [1] fused two-sweep Jacobi)
     int tz[2];           // z planes per wavefront (0: default rule)
+    int tz_restrict;     // coarse planes per wavefront of the fused residual + restriction (0: restrict_depth)
     int split[2];        // 1: an interior launch plus a border launch where the tiling allows
     const R *dinv[2];    // per node D^-1 of A_l ([0]) and B_l ([1]), complex interleaved; 0 on the boundary
     // FP32 levels: the interpolation coordinate before the clamp at eta* = 0.4, per node,

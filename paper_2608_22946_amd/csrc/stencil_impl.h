@@ -1208,19 +1208,14 @@ hipError_t launch_stencil(const LevelArgs<R> &L, const StencilCall &c, const Red
     // the Jacobi modes read the stored D^-1 of the operator
     if ((c.mode == M_JSWEEP || c.mode == M_JAC2 || c.mode == M_JAC2_ADD) && !L.dinv[c.shifted ? 1 : 0])
         return hipErrorInvalidValue;
-    const int fam = (c.mode == M_JAC2 || c.mode == M_JAC2_ADD) ? 1 : 0;
-    const int nyt = ceil_div(L.ny + 1, kWavesY);
-    const int tz = L.tz[fam] > 0 ? L.tz[fam] : pick_tz(ceil_div(L.nx + 1, kTileX), nyt, L.nz + 1);
     if (c.mode == M_RESID_R) {
         if (c.norm) return hipErrorInvalidValue;
-        TileMap M = {};   // x tiles of 60 columns, no edge tiles
-        M.rows = 1;
-        M.nxi = std::max(1, ceil_div((L.nx >> 1) - 1, 30));
-        M.nyt = nyt;
-        M.tz = std::max(1, tz / 2);   // coarse planes per chunk
-        M.total_blocks = M.nxi * nyt * ceil_div(L.nz >> 1, M.tz);
+        const int depth = L.tz_restrict > 0 ? L.tz_restrict : restrict_depth(L.nx, L.ny, L.nz, cur_batch().n);
+        const TileMap M = restrict_tiles(L.nx, L.ny, L.nz, depth);
         return launch_stencil_part<R, TX, TG, TY, 0>(L, c, rb, M, M.total_blocks, s);
     }
+    const int fam = (c.mode == M_JAC2 || c.mode == M_JAC2_ADD) ? 1 : 0;
+    const int tz = L.tz[fam] > 0 ? L.tz[fam] : pick_tz(ceil_div(L.nx + 1, kTileX), ceil_div(L.ny + 1, kWavesY), L.nz + 1);
     TileMap M = make_tiles(L.nx, L.ny, L.nz, L.lox, L.hix, tz);
     if (c.norm && M.total_blocks > rb.cap) return hipErrorInvalidValue;   // a partial a block
     if (L.split[fam] && M.strip) {

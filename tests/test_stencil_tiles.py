@@ -75,6 +75,28 @@ int main() {
 """
 
 
+# the chunks of the fused restriction hold every coarse plane at the depth that the rule takes
+RESTRICT_PROGRAM = r"""
+#include <cstdio>
+#include "tiles.h"
+using namespace helm;
+int main() {
+    for (int nx : {4, 8, 62, 64, 100, 352, 4096})
+        for (int ny : {4, 9, 40, 352, 4096})
+            for (int nz = 4; nz <= 400; nz += 2)
+                for (int slots : {1, 3, 8}) {
+                    const int d = restrict_depth(nx, ny, nz, slots);
+                    const TileMap M = restrict_tiles(nx, ny, nz, d);
+                    const int chunks = M.total_blocks / (M.nxi * M.nyt);
+                    if (d < 1 || d > 32 || M.tz != d || chunks * d < nz / 2 || (chunks - 1) * d >= nz / 2 ||
+                        30 * M.nxi < nx / 2 - 1 || kWavesY * M.nyt < ny + 1)
+                        return std::printf("%d x %d x %d, %d slots: depth %d, %d chunks\n", nx, ny, nz, slots, d, chunks);
+                }
+    return 0;
+}
+"""
+
+
 def _run(tmp_path, program):
     src, exe = tmp_path / "tiles.cpp", tmp_path / "tiles"
     src.write_text(program)
@@ -86,6 +108,28 @@ def _run(tmp_path, program):
 
 def test_marches_read_inside_the_grid(tmp_path):
     _run(tmp_path, ROWS_PROGRAM)
+
+
+def test_restriction_chunks_hold_every_plane(tmp_path):
+    _run(tmp_path, RESTRICT_PROGRAM)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("shape,n_pml", [((20, 12, 28), 4), ((56, 20, 60), 4), ((116, 12, 20), 6), ((16, 8, 92), 4)])
+def test_restriction_at_its_own_depth(shape, n_pml, precision):
+    """The fused residual + restriction where no depth is fixed, against the FP64 oracle
+    (the bars of the stencil kernels)."""
+    from tests.test_gpu_parity import Pair, rel, to_np
+    from workloads import grf_velocity
+    vel = grf_velocity(*shape, seed=81, corr_len=6.0)
+    p = Pair(vel, n_pml, precision)
+    for level in (0, 1):
+        g, z = p.rand(level, 401), p.rand(level, 402)
+        for op in (0, 1):
+            ref = p.o.restrict(level, p.o.residual(level, op, g.astype(complex), z.astype(complex)))
+            err = rel(to_np(p.g.residual_restrict(level, op, p.dev(g), p.dev(z))), ref)
+            assert err <= p.tol(1e-12, 1e-6), (level, op, err)
 
 
 @pytest.mark.gpu
