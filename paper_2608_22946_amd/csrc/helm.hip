@@ -356,7 +356,7 @@ void fill_level_args(helm_hierarchy *H, int l, LevelArgs<R> &L, const R *wx, con
     L.omega_ell = (R)(H->omega * g.ell);
     L.inv_ell2 = (R)(1.0 / (g.ell * g.ell));
     L.sigma = (R)H->opt.sigma;
-    L.tz[0] = L.tz[1] = 0;
+    L.tz[0] = L.tz[1] = L.tz_restrict = 0;
     L.split[0] = L.split[1] = 0;
     // D^-1 exists in the working precision only (the other LevelArgs serve the
     // FP64 outer residual and Q_h, which do not use it)
@@ -421,6 +421,13 @@ struct Eng {
     hipError_t stencil(int l, int mode, bool shifted, double wJ, const void *x, const void *g, const void *base,
                        void *y, bool norm = false, KState *st = nullptr) {
         StencilCall c{mode, shifted ? 1 : 0, wJ, x, g, base, y, norm, EPI_NORM_INIT, st, 0};
+        return launch_stencil<R, T, T, T>(L(l), c, Ln->rb, s);
+    }
+
+    // an apply or residual on its own (no other kernel of a map reads y next)
+    hipError_t stencil_alone(int l, int mode, bool shifted, const T *x, const T *g, T *y) {
+        StencilCall c{mode, shifted ? 1 : 0, 0.0, x, g, nullptr, y, false, EPI_NORM_INIT, nullptr, 0};
+        c.stream = stream_result(nn(l) * (long long)((g ? 3 : 2) * sizeof(T) + sizeof(float)));
         return launch_stencil<R, T, T, T>(L(l), c, Ln->rb, s);
     }
 
@@ -1634,7 +1641,7 @@ helm_status helm_apply(helm_hierarchy *H, int level, int op, const void *x, void
         if (op == HELM_OP_DA || op == HELM_OP_DQ)
             return launch_apply_dm<RR, TT>(E.L(0), op == HELM_OP_DQ, (const TT *)x, (TT *)y, E.s);
         if (op == HELM_OP_A || op == HELM_OP_B)
-            return E.stencil(level, M_APPLY, op == HELM_OP_B, 0.0, x, nullptr, nullptr, y);
+            return E.stencil_alone(level, M_APPLY, op == HELM_OP_B, (const TT *)x, nullptr, (TT *)y);
         if (op == HELM_OP_Q)
             return launch_qapply<typename T::R, TT, TT>(E.L(0), (const TT *)x, (TT *)y, E.s);
         return launch_diag<typename T::R, TT>(E.L(level), op == HELM_OP_DIAG_B, (const TT *)x, (TT *)y, E.s);
@@ -1645,7 +1652,10 @@ helm_status helm_residual(helm_hierarchy *H, int level, int op, const void *g, c
     if (!H) return fail(nullptr, HELM_EINVAL, "hierarchy is NULL");
     if (!level_ok(level) || (op != HELM_OP_A && op != HELM_OP_B) || !g || !x || !r || r == x || r == g)
         return fail(H, HELM_EINVAL, "invalid residual arguments");
-    return dispatch(H, [&](auto E) { return E.stencil(level, M_RESID, op == HELM_OP_B, 0.0, x, g, nullptr, r); });
+    return dispatch(H, [&](auto E) {
+        using TT = typename std::remove_reference<decltype(*E.v(nullptr))>::type;
+        return E.stencil_alone(level, M_RESID, op == HELM_OP_B, (const TT *)x, (const TT *)g, (TT *)r);
+    });
 }
 
 helm_status helm_residual_restrict(helm_hierarchy *H, int level, int op, const void *g, const void *x, void *coarse) {

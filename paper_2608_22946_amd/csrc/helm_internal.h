@@ -230,6 +230,7 @@ struct StencilCall {
     KState *st;
     int k;
     Scale sx = {1.0f, nullptr}, sg = {1.0f, nullptr}, sb = {1.0f, nullptr}, sy = {1.0f, nullptr};   // c16 operands
+    bool stream = false; // y stored past the caches (APPLY, RESID without the norm)
 };
 
 // R = arithmetic type, TX/TG/TY = element types of x, g, y (c32 or c64)
@@ -322,7 +323,7 @@ hipError_t launch_grad_phys(const double *gacc, const Geom &fine, int n_pml, con
 
 // z planes per stencil wavefront: any depth kTzMin..kTzMax may be fixed; setup times the candidates
 constexpr int kTzMin = 2, kTzMax = 64;
-constexpr int kTzCandidates[] = {2, 3, 4, 5, 6, 8, 10, 12, 14, 16, 20, 24, 32, 40, 48, 64};
+constexpr int kTzCandidates[] = {2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32, 40, 48, 64};
 
 template <typename TI, typename TO>
 hipError_t launch_convert(const TI *x, TO *y, long long n, hipStream_t s);

@@ -501,14 +501,14 @@ __device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t b, unsigned lane_of
 // and 415 us, residual 563 and 531, J2 631 and 589).
 template <typename T>
 constexpr bool split_row() { return sizeof(T) <= 8; }
-template <typename T>
+template <int HINT = 0, typename T>   // HINT 2: non-temporal
 __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t b, unsigned off, unsigned row_off, T v) {
     if constexpr (sizeof(T) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, off, row_off, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b, off, row_off, HINT);
     else if constexpr (sizeof(T) == 8)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, off, row_off, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), b, off, row_off, HINT);
     else
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, off, 0, 0);   // row_off: 0
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, off, 0, HINT);   // row_off: 0
 }
 // lane and row offsets of the stores of a row (nodes lx of the lane, r0 of the row); lanes without an output: kNoStore
 template <typename T>
@@ -527,6 +527,9 @@ constexpr bool own_dinv(int mode, bool shifted) {
     return scaled_coordinate<R>() && !shifted && mode == M_JAC2;
 }
 
+// modes whose result may be stored past the caches (a second store in the others costs registers)
+constexpr bool may_stream(int mode, bool norm) { return mode == M_APPLY || (mode == M_RESID && !norm); }
+
 // One wavefront: rows y-1, y, y+1 at 64 consecutive x, marching planes z0..z1-1.
 // Every load reads an in-bounds node (indices clamped to the grid) and
 // boundary / out-of-box values are masked to zero afterwards, so the loads
@@ -539,7 +542,7 @@ template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIF
 __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, const R *ctab, const TX *__restrict__ x,
                                       const TG *__restrict__ g, const TY *__restrict__ base, TY *__restrict__ y,
                                       R omegaJ, const R (&mul)[4], int xg, int yg, int z0, int z1, bool out_lane,
-                                      double &nrm, int Z0 = 0) {
+                                      double &nrm, bool stream, int Z0 = 0) {
     static_assert(!INNER || (XI && YI), "inner tiles have no stretching");
     // mul: multipliers of the c16 operands (x, g, base loads; y store), 1 for the others
     const R mx = mul[0], mg = mul[1], mb = mul[2], my = mul[3];
@@ -717,7 +720,11 @@ __device__ __forceinline__ void march(const LevelArgs<R> &L, const R *etab, cons
                 res.r += o.bc.r;
                 res.i += o.bc.i;
             }
-            buf_store(plane_buf(y + (unsigned long long)(unsigned)z * sy, sy), store_off, store_row, qz<TY>(res, my));
+            const auto yb = plane_buf(y + (unsigned long long)(unsigned)z * sy, sy);
+            if (may_stream(MODE, NORM) && stream)
+                buf_store<2>(yb, store_off, store_row, qz<TY>(res, my));
+            else
+                buf_store(yb, store_off, store_row, qz<TY>(res, my));
             if constexpr (NORM) {
                 if (out_lane) nrm += (double)res.r * (double)res.r + (double)res.i * (double)res.i;
             }
@@ -875,7 +882,7 @@ k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, co
             const bool inner = has_inner<R>(MODE, SHIFT) && xi && y_inner && z_inner(za, zb - 1) && xt >= 1 && 60 * xt + 62 <= L.nx - 1;
 #define HELM_MARCH_R(XI, YI, IN)                                                                                     \
     march<R, TX, TG, TY, MODE, SHIFT, false, XI, YI, IN>(L, etab, ctab, x, g, base, y, omegaJ, mul, xg, yg, za, zb, \
-                                                         false, nrm, Z0)
+                                                         false, nrm, false, Z0)
             if (inner)
                 HELM_MARCH_R(true, true, true);
             else if (xi && yi)
@@ -924,7 +931,7 @@ k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, co
     }
 #define HELM_MARCH(XI, YI, IN, YG)                                                                                   \
     march<R, TX, TG, TY, MODE, SHIFT, NORM, XI, YI, IN>(L, etab, ctab, x, g, base, y, omegaJ, mul, xg, YG, z0, z1,  \
-                                                        out, nrm)
+                                                        out, nrm, M.stream != 0)
     if (!rows_here)
         ;
     else if (has_inner<R>(MODE, SHIFT) && x_inner && y_inner && z_inner(z0, z1 - 1))
@@ -1218,6 +1225,7 @@ hipError_t launch_stencil(const LevelArgs<R> &L, const StencilCall &c, const Red
     const int tz = L.tz[fam] > 0 ? L.tz[fam] : pick_tz(ceil_div(L.nx + 1, kTileX), ceil_div(L.ny + 1, kWavesY), L.nz + 1);
     TileMap M = make_tiles(L.nx, L.ny, L.nz, L.lox, L.hix, tz);
     if (c.norm && M.total_blocks > rb.cap) return hipErrorInvalidValue;   // a partial a block
+    M.stream = c.stream;
     if (L.split[fam] && M.strip) {
         // groups of four rows all inside [loy, hiy]
         M.yt_lo = ceil_div(L.loy, kWavesY);

@@ -35,6 +35,7 @@ struct TileMap {
     int tz;
     int block_offset;      // index of this launch's first block among all blocks of the call
     int total_blocks;      // blocks over all launches of the call
+    int stream;            // 1: the result is stored past the caches (stream_result)
 };
 
 constexpr int kStrips[] = {30, 14, 6};
@@ -109,6 +110,13 @@ inline int restrict_depth(int nx, int ny, int nz, int slots) {
     }
     return best;
 }
+
+// Whether an apply or a residual on its own stores its result past the caches (non-temporal).  Inside the
+// nested maps the next kernel reads the result, and such stores make them slower (S_h at 176^3 260 -> 297 us).  A call
+// on its own that fits in the last-level cache (256 MB) leaves its operands there instead: B_h in FP32 at
+// 176^3 37.5 -> 29 us, A_2h of a 352^3 grid 37.5 -> 28.6, in FP64 at 144^3 39 -> 30.  Larger calls keep nothing
+// (256^3: 112 -> 117 us) and small ones nothing that matters (32^3: 3% slower).
+inline bool stream_result(long long bytes) { return bytes >= (16ll << 20) && bytes <= (256ll << 20); }
 
 // Rows and weight nodes that a wavefront reads.  A march goes past the grid on purpose (the last edge
 // tile's rows lie up to three beyond ny, the fused restriction starts at plane -1): the indices that
