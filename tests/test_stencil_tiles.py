@@ -133,6 +133,44 @@ def test_restriction_at_its_own_depth(shape, n_pml, precision):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("shape,n_pml", [((54, 10, 34), 5), ((58, 10, 14), 13), ((62, 6, 10), 29)])
+def test_pml_as_wide_as_the_strip(shape, n_pml, precision):
+    """Grids whose first column free of stretching is the first one of the inner tiles (strips of 6, 14 and 30
+    columns): the fused Jacobi must not form D^-1 in place there, because the column before is stretched."""
+    from tests.test_gpu_parity import Pair, rel, to_np
+    from workloads import grf_velocity
+    p = Pair(grf_velocity(*shape, seed=82, corr_len=6.0), n_pml, precision, tiling=dict(tile_tz=4, tile_split=0))
+    g = p.rand(0, 403)
+    for op in (0, 1):
+        for sweeps in (2, 3):
+            ref = p.o.jacobi(0, op, g.astype(complex), sweeps, 0.8)
+            err = rel(to_np(p.g.jacobi(0, op, p.dev(g), sweeps, 0.8)), ref)
+            assert err <= p.tol(1e-12, 1e-6), (op, sweeps, err)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("m_4h", [5, 6, 7, 8])
+def test_vcycle_is_its_steps(m_4h, precision):
+    """V^sigma_2h, which forms the bottom combination inside the prolongation and adds its last Jacobi onto the
+    iterate, against the same cycle from the entry points of its steps.  The coefficients of the combination are the
+    same; only a few sums round differently, so that long bases need no wider bar than the stencils."""
+    import torch
+    from tests.test_gpu_parity import Pair
+    from workloads import grf_velocity
+    p = Pair(grf_velocity(20, 12, 16, seed=83, corr_len=4.0), 4, precision, m_4h=m_4h)
+    q = p.dev(p.rand(1, 404))
+    w = p.g.opt.omega_2h
+    y = p.g.jacobi(1, 1, q, 2, w)
+    e = p.g.bottom(p.g.residual_restrict(1, 1, q, y))
+    p.g.prolong_add(2, e, y)
+    y = y + p.g.jacobi(1, 1, p.g.residual(1, 1, q, y), 2, w)
+    err = float(torch.linalg.vector_norm(p.g.vcycle(q) - y) / torch.linalg.vector_norm(y))
+    assert err <= p.tol(1e-12, 1e-6), err
+
+
+@pytest.mark.gpu
 def test_norm_of_more_blocks_than_the_least_partials():
     """620 x 16 x 3932 cells at two planes a wavefront: 102284 blocks, where the partials' least size is 98304.
     The norm that one preconditioner call reports is that of the residual of its result (both norms are of
