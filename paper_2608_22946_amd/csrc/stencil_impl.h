@@ -1,5 +1,5 @@
 // Implementation of the stencil kernels and their launcher templates, included by the
-// translation units that instantiate them (stencil.hip: FP32 / FP64 operands;
+// translation units that instantiate them (stencil.hip: FP32 operands; stencil_fp64.hip: FP64;
 // stencil_mixed.hip: the FP16-stored operands of the mixed-precision cycle).
 // Matrix-free 27-point IOFD level operator and its fused variants.
 //
@@ -770,13 +770,14 @@ constexpr int waves_per_simd() {
     return sizeof(R) == sizeof(float) ? 4 : 1;
 }
 
-// Whether a kernel has the INNER variant.  The unshifted FP32 apply and residuals run on the fine level,
-// where the memory path bounds them and waves of two speeds cost more than the shorter code gives
-// (352^3, with and without it: apply 246 and 239 us, residual 308 and 299, restricted 295 and 288;
-// the unshifted 2h apply takes 29 us either way).
+// Whether a kernel has the INNER variant: FP32 sweeps, fused Jacobi and shifted operators.  The unshifted FP32
+// apply and residuals run on the fine level, where the memory path bounds them and waves of two speeds cost
+// more than the shorter code gives (352^3, with and without it: apply 246 and 239 us, residual 308 and 299,
+// restricted 295 and 288; the unshifted 2h apply takes 29 us either way).  In FP64 it changes nothing (352^3
+// at the best depths: apply 419 and 421 us, residual 532 and 531, J2 589 and 587; S_h at 208^3 724 and 723).
 template <typename R>
 constexpr bool has_inner(int mode, bool shifted) {
-    return sizeof(R) != sizeof(float) || shifted || !(mode == M_APPLY || mode == M_RESID || mode == M_RESID_R);
+    return sizeof(R) == sizeof(float) && (shifted || !(mode == M_APPLY || mode == M_RESID || mode == M_RESID_R));
 }
 
 template <typename R, typename TX, typename TG, typename TY, int MODE, bool SHIFT, bool NORM, int PART>
