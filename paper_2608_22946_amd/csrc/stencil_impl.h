@@ -842,11 +842,17 @@ k_stencil(LevelArgs<R> L, const TX *__restrict__ x, const TG *__restrict__ g, co
             yt = v / M.nxi;
             if (yt >= M.yt_lo) yt += M.nyi;
         }
+    } else if (MODE == M_RESID_R) {
+        // no edge tiles: two divisions instead of four (32^3 to 132 x 40 x 48: 1 to 2% of the call)
+        xt = t % M.nxi;
+        t /= M.nxi;
+        yt = t % M.nyt;
+        zc = t / M.nyt;
     } else {
         // the blocks of neighbouring tiles follow each other, so that they run together and the cache
         // merges the sectors that two of them write: per `rows` groups of rows one edge block, then
         // their inner tiles, x fastest
-        const int ne = MODE != M_RESID_R && M.strip ? 1 : 0, unit = ne + M.rows * M.nxi;
+        const int ne = M.strip ? 1 : 0, unit = ne + M.rows * M.nxi;
         const int per_z = M.neb + M.nyt * M.nxi;   // the last unit of a chunk may be shorter
         zc = t / per_z;
         int v = t - zc * per_z;
