@@ -22,8 +22,8 @@
 //
 // What bounds it: the LDS (five 16-byte reads a node for the coefficients, three to six accesses for the
 // exchange) and the vector unit about equally, then the imbalance of the stretched blocks, which
-// take about twice the time of the others.  A^T at 216^3 145 -> 86 us in FP32 and 264 -> 193 us in
-// FP64, at 352^3 457 -> 290 and 840 -> 640 us, at 64^3 40 -> 11 and 47 -> 19 us, against a block of
+// take about twice the time of the others.  A^T at 216^3 145 -> 86 us in FP32 and 264 -> 189 us in
+// FP64, at 352^3 457 -> 290 and 840 -> 610 us, at 64^3 40 -> 11 and 47 -> 18 us, against a block of
 // 64 x 4 outputs that staged nine values a node in LDS and read 27 neighbours' terms from there.
 // Measured and not kept: eight rows a block (96 us at 216^3) and sixteen (104 us: one block a CU), the
 // quintic table of the shell coefficients (six reads a node: 290 -> 295 us at 352^3), and
